@@ -15,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmea.so")
-SOURCES = ["api.hip", "fwd.hip", "bwd.hip", "decode.hip"]
+SOURCES = ["bwd_bf16.hip", "bwd_f16.hip", "bwd_f32.hip", "fwd.hip", "decode.hip", "api.hip", "bwd.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -149,6 +149,55 @@ constexpr bool bwd_two_group(bool is16, int d, int dv, bool same_out_dtype, bool
   return bwd_two_group_exists(is16, d, dv, same_out_dtype) && !(causal && n_q <= MEA_T64_BWD_CAUSAL_SMALL) &&
          !(!causal && n_q <= MEA_T64_BWD_SHORT);
 }
+// Whether a problem with records runs the two-group kernels (256 keys or
+// queries per workgroup, one workgroup per CU) or the 4-wave kernels (128, two
+// per CU, dK/dV and dQ in one launch), which read records too and give bitwise
+// the same gradients while one wave takes all of a column's rows.  Below one
+// two-group round (256 workgroups) the 4-wave kernels fill more of the chip;
+// causal grids need two rounds before their uneven workgroups even out, and up
+// to 1024 unmasked queries the last 256-query tile is padding to a large part.
+// Measured, dK/dV + dQ + preprocess in us, 4-wave / two-group, bf16 d = 64:
+// unmasked 1x8x4096 (128 workgroups) 133 / 176, 1x10x4096 (160) 182 / 182,
+// 1x12x4096 (192) 211 / 187, 1x4x8192 (128) 241 / 330, 16x8x600 75 / 96,
+// 8x8x1024 (256) 78 / 77; causal 1x8x8192 (256) 287 / 357, 2x16x4096 (512)
+// 330 / 343, 1x16x8192 (512) 549 / 476, 1x8x16384 (512) 969 / 877.
+inline bool bwd_two_group_fills(bool causal, int64_t n_q, int64_t n_k, int64_t bh) {
+  const int64_t wq = bh * ((n_q + 255) / 256), wk = bh * ((n_k + 255) / 256);
+  if (!causal && n_q <= 1024) return false;
+  return (wq < wk ? wq : wk) >= (causal ? 512 : 160);
+}
+// Workgroups of the 4-wave backward kernels when every wave has 32 rows of its
+// own: 128 keys (dK/dV) or 128 queries (dQ) each.
+inline int64_t bwd_tiles128(int64_t n_q, int64_t n_k, int64_t bh) {
+  return bh * ((n_k + 127) / 128 + (n_q + 127) / 128);
+}
+// Waves of a 4-wave backward workgroup that share one 32-key column (dK/dV) or
+// one set of 32 queries (dQ) and split the streamed rows between them: 4 or 2
+// where 128-row workgroups would leave CUs idle.  Each such workgroup streams
+// all rows for fewer columns, so it pays only until the chip is full; a causal
+// problem is half as full as its tiles suggest once the tiles are many.  At
+// d = 128 the wider stages leave LDS for two waves and one workgroup per CU.
+// Measured, backward in us with 1 / 2 / 4 waves, bf16: d = 64 1x1x4096 (64
+// tiles of 128) 99 / 80 / 55, 1x8x1024 (128) 30 / 25 / 20, 2x8x1024 (256) 32 /
+// 28 / 37, 1x4x4096 (256) 96 / 83 / 103, 3x8x1024 (384) 38 / 43 / 52; causal
+// 1x8x4096 (512) 109 / 90 / 118, 4x8x1024 (512) 37 / 42 / 53, 2x8x4096 (1024)
+// 171 / 172 / 230; d = 128 2x8x512 (128) 32 / 25, causal 1x8x2000 (256) 101 /
+// 68, unmasked 87 / 101, causal 1x12x2000 (384) 109 / 111.
+inline int bwd_stream_waves(bool causal, int dmax, int64_t n_q, int64_t n_k, int64_t bh) {
+  int64_t tiles = bwd_tiles128(n_q, n_k, bh);
+  if (causal && n_q > 1024) tiles /= 2;
+  if (dmax == 128) return tiles <= 128 ? 2 : 1;
+  return tiles <= 128 ? 4 : (tiles <= 256 ? 2 : 1);
+}
+// Whether dK/dV and dQ run in one launch (4-wave kernels, one wave per
+// column): faster wherever the two grids can fill each other's gaps, on large
+// grids at d = 128 the mixed register allocation costs more.  Separate / one
+// launch: d = 64 1x1x4096 162 / 99 us, 8x8x1024 causal 74 / 65, 32x32x1024
+// causal 893 / 859; d = 128 8x16x2048 causal (4096 tiles) 647 / 622, 4x32x4096
+// causal (8192) 2014 / 2042, 4x32x8192 causal 7280 / 7515.
+inline bool bwd_one_launch(int dmax, int64_t n_q, int64_t n_k, int64_t bh) {
+  return dmax == 64 || bwd_tiles128(n_q, n_k, bh) <= 4096;
+}
 // dtype: 0 float32, 1 fp16, 2 bf16; d and dv the head dimensions of q, k and
 // of v, o.
 inline bool bwd_uses_row_records(int dtype, int d, int dv, bool out_f32, bool causal, int64_t n_q) {
