@@ -2,14 +2,19 @@
 
 Only argument marshalling lives here.  The library is loaded from this package
 directory; if it is missing the call fails loudly -- there is no fallback.
+``native()`` is the extension module that marshals torch tensors into the same
+library without Python in between (``csrc/torch_ext.cpp``).
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libmea.so")
+EXT_PATH = os.path.join(HERE, "_torch_ext.so")
 
 MEA_OK = 0
 MEA_ERR_INVALID_ARG = 1
@@ -98,6 +103,27 @@ def load(path: str = LIB_PATH):
     lib.mea_status_string.restype = ctypes.c_char_p
     _lib = lib
     return lib
+
+
+_native = None
+
+
+def native():
+    """The extension module, bound to the library of ``load()`` (once)."""
+    global _native
+    if _native is None:
+        lib = load()
+        if not os.path.exists(EXT_PATH):
+            raise ImportError("_torch_ext.so not found at %s: build it with `python -m paper_2112_05682_amd.build`"
+                              % EXT_PATH)
+        loader = importlib.machinery.ExtensionFileLoader(__package__ + "._torch_ext", EXT_PATH)
+        ext = importlib.util.module_from_spec(importlib.util.spec_from_loader(loader.name, loader))
+        loader.exec_module(ext)
+        ext.init(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+                   for name in ("mea_attention_fwd_workspace_size", "mea_attention_bwd_workspace_size",
+                                "mea_attention_fwd", "mea_attention_bwd")))
+        _native = ext
+    return _native
 
 
 def status_string(status: int) -> str:

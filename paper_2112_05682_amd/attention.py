@@ -1,6 +1,9 @@
 """PyTorch-facing wrapper of the C ABI: allocation of outputs and workspace
 through torch, and the current HIP stream.  Every step of the computation runs
-in the HIP kernels of ``libmea.so``; nothing here computes attention.
+in the HIP kernels of ``libmea.so``; nothing here computes attention.  Plain
+GPU tensors that the kernels can use in place take one native call
+(``_lib.native()``, which returns None for anything else); the Python below it
+handles every other input, and says what is wrong with those it refuses.
 
 Tensors are ``[B, H, n, d]`` on one GPU with contiguous features; their batch,
 head and row strides are passed to the kernels, so views such as the paper's
@@ -91,6 +94,9 @@ def attention_fwd(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, causal: boo
     rounding residual (contiguous, o's dtype), which the backward uses to form
     D_i = do_i . o_i accurately where the softmax saturates; None for a
     float32 o."""
+    r = _lib.native().fwd(q, k, v, causal, scale, need_lse, out, out_dtype, kv_len, residual)
+    if r is not None:
+        return r
     if k.shape[:3] != v.shape[:3] or q.shape[:2] != k.shape[:2] or q.shape[3] != k.shape[3]:
         raise ValueError("shape mismatch: q %s k %s v %s" % (tuple(q.shape), tuple(k.shape),
                                                               tuple(v.shape)))
@@ -127,6 +133,9 @@ def attention_bwd(q, k, v, o, lse, do, causal: bool = False, scale: float | None
     ``kv_len`` must be the forward's; masked keys get zero dk and dv rows.
     ``o_lo``: the forward's residual of a 16-bit o (``attention_fwd(...,
     residual=True)``); without it D_i is formed from the rounded o alone."""
+    r = _lib.native().bwd(q, k, v, o, lse, do, causal, scale, need_dq, need_dkdv, out, kv_len, o_lo)
+    if r is not None:
+        return r
     _check_tensors(("q", "k", "v"), (q, k, v), q.dtype, q.device)
     if o.dtype not in (q.dtype, torch.float32):
         raise TypeError("o must have q's dtype or float32")
@@ -173,9 +182,12 @@ class MemoryEfficientAttention(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, q, k, v, causal=False, scale=None, out_dtype=None, kv_len=None):
-        q, k, v = (_feature_contiguous(t) for t in (q, k, v))
-        o, lse, o_lo = attention_fwd(q, k, v, causal, scale, need_lse=True, out_dtype=out_dtype,
-                                     kv_len=kv_len, residual=True)
+        r = _lib.native().fwd(q, k, v, causal, scale, True, None, out_dtype, kv_len, True)
+        if r is None:
+            q, k, v = (_feature_contiguous(t) for t in (q, k, v))
+            r = attention_fwd(q, k, v, causal, scale, need_lse=True, out_dtype=out_dtype, kv_len=kv_len,
+                              residual=True)
+        o, lse, o_lo = r
         ctx.save_for_backward(q, k, v, o, lse, o_lo)
         ctx.causal = causal
         ctx.scale = scale
@@ -185,9 +197,11 @@ class MemoryEfficientAttention(torch.autograd.Function):
     @staticmethod
     def backward(ctx, do):
         q, k, v, o, lse, o_lo = ctx.saved_tensors
-        dq, dk, dv = attention_bwd(q, k, v, o, lse, _feature_contiguous(do.to(o.dtype)), ctx.causal,
-                                   ctx.scale, kv_len=ctx.kv_len, o_lo=o_lo)
-        return dq, dk, dv, None, None, None, None
+        r = _lib.native().bwd(q, k, v, o, lse, do, ctx.causal, ctx.scale, True, True, None, ctx.kv_len, o_lo)
+        if r is None:
+            r = attention_bwd(q, k, v, o, lse, _feature_contiguous(do.to(o.dtype)), ctx.causal, ctx.scale,
+                              kv_len=ctx.kv_len, o_lo=o_lo)
+        return (*r, None, None, None, None)
 
 
 def _feature_contiguous(t: torch.Tensor) -> torch.Tensor:
@@ -210,14 +224,18 @@ class PackedQKVAttention(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, qkv, causal=False, scale=None, kv_len=None):
-        if qkv.dim() != 5 or qkv.shape[2] != 3:
-            raise ValueError("qkv must be [B, n, 3, H, d]")
-        qkv = qkv if qkv.is_contiguous() else qkv.contiguous()
-        B, n, _, H, d = qkv.shape
-        q, k, v = (qkv[:, :, i].transpose(1, 2) for i in range(3))  # [B, H, n, d] views
-        o = torch.empty(B, n, H, d, dtype=qkv.dtype, device=qkv.device)
-        _, lse, o_lo = attention_fwd(q, k, v, causal, scale, need_lse=True, out=o.transpose(1, 2),
-                                     kv_len=kv_len, residual=True)
+        r = _lib.native().packed_fwd(qkv, causal, scale, kv_len)
+        if r is None:
+            if qkv.dim() != 5 or qkv.shape[2] != 3:
+                raise ValueError("qkv must be [B, n, 3, H, d]")
+            qkv = qkv if qkv.is_contiguous() else qkv.contiguous()
+            B, n, _, H, d = qkv.shape
+            q, k, v = (qkv[:, :, i].transpose(1, 2) for i in range(3))  # [B, H, n, d] views
+            o = torch.empty(B, n, H, d, dtype=qkv.dtype, device=qkv.device)
+            _, lse, o_lo = attention_fwd(q, k, v, causal, scale, need_lse=True, out=o.transpose(1, 2),
+                                         kv_len=kv_len, residual=True)
+        else:
+            o, lse, o_lo = r
         ctx.save_for_backward(qkv, o, lse, o_lo)
         ctx.causal, ctx.scale, ctx.kv_len = causal, scale, kv_len
         return o
@@ -225,6 +243,9 @@ class PackedQKVAttention(torch.autograd.Function):
     @staticmethod
     def backward(ctx, do):
         qkv, o, lse, o_lo = ctx.saved_tensors
+        dqkv = _lib.native().packed_bwd(qkv, o, lse, o_lo, do, ctx.causal, ctx.scale, ctx.kv_len)
+        if dqkv is not None:
+            return dqkv, None, None, None
         q, k, v = (qkv[:, :, i].transpose(1, 2) for i in range(3))
         dqkv = torch.empty_like(qkv)
         dq, dk, dv = (dqkv[:, :, i].transpose(1, 2) for i in range(3))

@@ -1,7 +1,10 @@
-"""Build of the HIP library ``libmea.so`` (gfx950) from ``csrc/*.hip``.
+"""Build of the HIP library ``libmea.so`` (gfx950) from ``csrc/*.hip`` and of
+the torch extension ``_torch_ext.so`` from ``csrc/torch_ext.cpp``.
 
-Every translation unit is compiled by hipcc for gfx950 only and linked into one
-shared library placed next to this file, so it travels with the source tree.
+Every translation unit of the library is compiled by hipcc for gfx950 only and
+linked into one shared library.  The extension is host code (g++) that links to
+torch and is given the library's addresses when it is loaded.  Both are placed
+next to this file, so they travel with the source tree.
 """
 from __future__ import annotations
 
@@ -9,12 +12,14 @@ import concurrent.futures as cf
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmea.so")
+EXT = os.path.join(HERE, "_torch_ext.so")
 SOURCES = ["bwd_bf16.hip", "bwd_f16.hip", "bwd_f32.hip", "fwd.hip", "decode.hip", "api.hip", "bwd.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -39,10 +44,30 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_ext() -> None:
+    import torch
+
+    t = os.path.dirname(torch.__file__)
+    tmp = EXT + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-I" + os.path.join(t, "include"), "-I" + os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(os.path.dirname(HIPCC), "..", "include"),
+           os.path.join(CSRC, "torch_ext.cpp"), "-o", tmp,
+           "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for torch_ext.cpp:\n" + r.stderr)
+    os.replace(tmp, EXT)
+
+
 def build() -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        ext = ex.submit(_build_ext)
         objs = list(ex.map(_compile, SOURCES))
+        ext.result()
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)
