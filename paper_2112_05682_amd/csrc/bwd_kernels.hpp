@@ -172,25 +172,25 @@ struct DkdvTile {
   static constexpr int NT = 256;
   static constexpr int BKG = 128 / SW;      // keys per workgroup
   static constexpr int BQ = 32 * QS * SW;   // queries per iteration
-  static constexpr int E = sizeof(T);
-  static constexpr int RSQ = D + 16 / E;        // LDS row strides (elements), 16 B pad
-  static constexpr int RSO = DV + 16 / E;
-  static constexpr int TILEQ = BQ * RSQ;        // Q tile (elements)
-  static constexpr int TILEO = BQ * RSO;        // dO tile
-  static constexpr int CPRQ = D * E / 16;
-  static constexpr int CPRO = DV * E / 16;
+  static constexpr int E = 2;                   // bytes of an LDS element
+  static constexpr int NP = Planes<T>::NP;      // planes of a tile
+  static constexpr int RSQ = D + 8;             // LDS row strides (elements), 16 B pad
+  static constexpr int RSO = DV + 8;
+  static constexpr int TILEQ = BQ * RSQ;        // one plane of the Q tile (elements)
+  static constexpr int TILEO = BQ * RSO;        // of the dO tile
+  static constexpr int CPRQ = D / 8;            // 8-element chunks per row
+  static constexpr int CPRO = DV / 8;
   static constexpr int CHUNKS = BQ * (CPRQ + CPRO);  // Q and dO chunks per stage
   static constexpr int CPT = (CHUNKS + NT - 1) / NT;
-  static constexpr int STAGE_ELEMS = TILEQ + TILEO;
+  static constexpr int STAGE_ELEMS = NP * (TILEQ + TILEO);
   static constexpr int STAGE_BYTES = STAGE_ELEMS * E + 2 * BQ * 4;  // + accumulator initial values
-  static constexpr int LDS_BYTES = 2 * STAGE_BYTES;
   // With K_LDS the K fragments of every lane follow the two stages.
   static constexpr int KSLOT_BYTES = NT * (D / 16) * 16;
-  static constexpr bool k_lds(int occ) { return E == 2 && D == 128 && occ == 2; }
+  static constexpr bool k_lds(int occ) { return sizeof(T) == 2 && D == 128 && occ == 2; }
   // Asynchronous stage copies (16-bit, d = 128, dO in the input dtype): each
   // tile is a whole number of 1 KiB copy units, one 16-byte slot per row chunk
   // plus one for the row pad.
-  static constexpr bool async(bool same_out) { return E == 2 && D == 128 && same_out; }
+  static constexpr bool async(bool same_out) { return sizeof(T) == 2 && D == 128 && same_out; }
   static constexpr int UQ = (BQ * (CPRQ + 1) * 16 + 1023) / 1024;
   static constexpr int UO = (BQ * (CPRO + 1) * 16 + 1023) / 1024;
   static constexpr int ASTAGE_BYTES = (UQ + UO) * 1024 + 2 * BQ * 4;
@@ -207,8 +207,12 @@ struct DkdvTile {
   // SW > 1: the waves' partial dK and dV (float32) pass through the stages'
   // space after the last tile.
   static constexpr int RED_BYTES = (4 / SW) * (SW - 1) * ((D + DV) / 32) * 16 * 64 * 4;
+  // Two stages where they fit (float32 at 128 rows or features: one).
+  static constexpr int nbuf(int occ, bool same_out) {
+    return 2 * stage_bytes(same_out) + (k_lds(occ) ? KSLOT_BYTES : 0) <= 160 * 1024 / occ ? 2 : 1;
+  }
   static constexpr int lds_bytes(int occ, bool same_out) {
-    const int b = 2 * stage_bytes(same_out) + (k_lds(occ) ? KSLOT_BYTES : 0);
+    const int b = nbuf(occ, same_out) * stage_bytes(same_out) + (k_lds(occ) ? KSLOT_BYTES : 0);
     return b > RED_BYTES ? b : RED_BYTES;
   }
 };
@@ -254,6 +258,7 @@ __device__ __forceinline__ Frag<T> lds_col_frag_swz128(const T* tile, int row0, 
 template <typename T, typename TO, int D, int DV, int QS, int SW, int OCC, bool CAUSAL>
 __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
   using Cfg = DkdvTile<T, D, DV, QS, SW>;
+  using LE = typename Planes<T>::E;  // element of an LDS tile
   constexpr int KWAVES = 4 / SW;  // 32-key columns of the workgroup
   constexpr int RSQ = Cfg::RSQ, RSO = Cfg::RSO;
   constexpr int KC = D / 16, KCV = DV / 16;
@@ -291,21 +296,17 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
   constexpr bool SWZ = Cfg::swz(__is_same(T, TO));
   constexpr int STAGE_B = Cfg::stage_bytes(__is_same(T, TO));
   constexpr int UQ = SWZ ? Cfg::SUQ : Cfg::UQ, UO = SWZ ? Cfg::SUO : Cfg::UO;  // 1 KiB copy units
-  constexpr int TILEQ_L = ASYNC ? UQ * 1024 / Cfg::E : Cfg::TILEQ;  // dO tile offset (elements)
+  constexpr int TILEQ_L = ASYNC ? UQ * 1024 / Cfg::E : Cfg::NP * Cfg::TILEQ;  // dO tile offset (elements)
+  constexpr int NBUF = Cfg::nbuf(OCC, __is_same(T, TO));
+  static_assert(!ASYNC || NBUF == 2, "asynchronous copies need two stages");
   constexpr int INIT_OFF = ASYNC ? (UQ + UO) * 1024 : Cfg::STAGE_ELEMS * Cfg::E;
   constexpr bool ILV = MEA_DKDV_ILV && sizeof(T) == 2;
   constexpr int KV_AHEAD = MEA_T128_DKDV_AHEAD;
-  T* const kslot = reinterpret_cast<T*>(smem_raw + 2 * STAGE_B) + 8 * tid;
+  T* const kslot = reinterpret_cast<T*>(smem_raw + NBUF * STAGE_B) + 8 * tid;
   Frag<T> kf[K_LDS ? 1 : KC], vf[KCV];
 #pragma unroll
   for (int kc = 0; kc < KC; ++kc) {
-    Frag<T> f;
-    if (key < p.n_k) {
-      f = *reinterpret_cast<const Frag<T>*>(kg + key * p.sk.r + 16 * kc + 8 * h);
-    } else {
-#pragma unroll
-      for (int s = 0; s < 8; ++s) f[s] = (T)0.0f;
-    }
+    const Frag<T> f = key < p.n_k ? ld_frag_as<T, T>(kg + key * p.sk.r + 16 * kc + 8 * h) : zero_frag<T>();
     if constexpr (K_LDS) *reinterpret_cast<Frag<T>*>(kslot + 8 * Cfg::NT * kc) = f;
     else kf[kc] = f;
   }
@@ -314,14 +315,8 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
     else return kf[kc];
   };
 #pragma unroll
-  for (int kc = 0; kc < KCV; ++kc) {
-    if (key < p.n_k) {
-      vf[kc] = *reinterpret_cast<const Frag<T>*>(vg + key * p.sv.r + 16 * kc + 8 * h);
-    } else {
-#pragma unroll
-      for (int s = 0; s < 8; ++s) vf[kc][s] = (T)0.0f;
-    }
-  }
+  for (int kc = 0; kc < KCV; ++kc)
+    vf[kc] = key < p.n_k ? ld_frag_as<T, T>(vg + key * p.sv.r + 16 * kc + 8 * h) : zero_frag<T>();
 
   wait_global_loads();
 
@@ -348,11 +343,11 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
   // allow two sets: float32, or two waves per SIMD) loads the next tile at the
   // start of the iteration that writes it.
   constexpr int PF = sizeof(T) == 2 && OCC == 1 && !ASYNC ? 2 : 1;
-  u32x4 stage_a[Cfg::CPT], stage_b[Cfg::CPT];
+  Chunk8<T> stage_a[Cfg::CPT], stage_b[Cfg::CPT];
   float stage_fa = 0.0f, stage_fb = 0.0f;
   auto stage_base = [&](int buf) { return smem_raw + buf * STAGE_B; };
   auto load_stage = [&](auto set_tag, int64_t q0) __attribute__((always_inline)) {
-    u32x4 (&stage)[Cfg::CPT] = decltype(set_tag)::value ? stage_b : stage_a;
+    Chunk8<T> (&stage)[Cfg::CPT] = decltype(set_tag)::value ? stage_b : stage_a;
     float& stage_f = decltype(set_tag)::value ? stage_fb : stage_fa;
 #pragma unroll
     for (int i = 0; i < Cfg::CPT; ++i) {
@@ -364,11 +359,11 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
         const int cpr = is_o ? Cfg::CPRO : Cfg::CPRQ;
         const int row = rem / cpr, col = rem % cpr;
         const int64_t q = q0 + row;
-        const int64_t coff = col * (16 / Cfg::E);
+        const int64_t coff = 8 * col;
         if (q >= p.n_q)
-          stage[i] = u32x4{0u, 0u, 0u, 0u};
+          stage[i] = zero_chunk8<T>();
         else
-          stage[i] = is_o ? ld_chunk_as<T, TO>(dog + q * p.sdo.r + coff) : ld16(qg + q * p.sq.r + coff);
+          stage[i] = is_o ? ld_chunk8<T, TO>(dog + q * p.sdo.r + coff) : ld_chunk8<T, T>(qg + q * p.sq.r + coff);
       }
     }
     if (tid < 2 * Cfg::BQ) {
@@ -376,9 +371,9 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
     }
   };
   auto store_stage = [&](auto set_tag, int buf) __attribute__((always_inline)) {
-    const u32x4 (&stage)[Cfg::CPT] = decltype(set_tag)::value ? stage_b : stage_a;
+    const Chunk8<T> (&stage)[Cfg::CPT] = decltype(set_tag)::value ? stage_b : stage_a;
     const float stage_f = decltype(set_tag)::value ? stage_fb : stage_fa;
-    T* base = reinterpret_cast<T*>(stage_base(buf));
+    LE* base = reinterpret_cast<LE*>(stage_base(buf));
 #pragma unroll
     for (int i = 0; i < Cfg::CPT; ++i) {
       const int chunk = tid + i * Cfg::NT;
@@ -387,7 +382,8 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
         const int rem = is_o ? chunk - Cfg::BQ * Cfg::CPRQ : chunk;
         const int cpr = is_o ? Cfg::CPRO : Cfg::CPRQ;
         const int row = rem / cpr, col = rem % cpr;
-        st16(base + (is_o ? Cfg::TILEQ + row * RSO : row * RSQ) + col * (16 / Cfg::E), stage[i]);
+        st_chunk8<T>(base + (is_o ? Cfg::NP * Cfg::TILEQ + row * RSO : row * RSQ) + 8 * col,
+                     is_o ? Cfg::TILEO : Cfg::TILEQ, stage[i]);
       }
     }
     if (tid < 2 * Cfg::BQ) {
@@ -486,13 +482,15 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
     // The wave's rows of the tile: qsub .. qsub + 32 QS - 1 (a multiple of 32,
     // so the row swizzle is that of the tile).
     const int64_t q0 = q_begin + (int64_t)it * Cfg::BQ + qsub;
-    const T* qs_t = reinterpret_cast<const T*>(stage_base(it & 1)) + qsub * (SWZ ? D : RSQ);
-    const T* dos_t = reinterpret_cast<const T*>(stage_base(it & 1)) + TILEQ_L + qsub * (SWZ ? DV : RSO);
-    const float* sinit_s = reinterpret_cast<const float*>(stage_base(it & 1) + INIT_OFF) + qsub;
+    const int buf = it & (NBUF - 1);
+    const LE* qs_t = reinterpret_cast<const LE*>(stage_base(buf)) + qsub * (SWZ ? D : RSQ);
+    const LE* dos_t = reinterpret_cast<const LE*>(stage_base(buf)) + TILEQ_L + qsub * (SWZ ? DV : RSO);
+    const float* sinit_s = reinterpret_cast<const float*>(stage_base(buf) + INIT_OFF) + qsub;
     const float* dpinit_s = sinit_s + Cfg::BQ;
 
     // Nothing to do when every query of the tile precedes this wave's keys.
-    const bool active = !CAUSAL || q0 + 32 * QS - 1 >= kw;
+    // (float32 has no registers for the branch: it masks those few tiles.)
+    const bool active = !CAUSAL || sizeof(T) == 4 || q0 + 32 * QS - 1 >= kw;
     if (active) {
       // Accumulators start at -lse/scale and -D of their query rows (register r
       // of lane half h holds query 32 qs + permuted_row(r, h)).
@@ -537,13 +535,15 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) {
           if (kc < KC) {
-            const Frag<T> a = SWZ ? lds_frag_swz128<T>(qs_t, 32 * qs + qrow, 2 * kc + h)
-                                  : lds_frag<T>(qs_t + (32 * qs + qrow) * RSQ + 16 * kc + 8 * h);
+            Frag<T> a;
+            if constexpr (SWZ) a = lds_frag_swz128<T>(qs_t, 32 * qs + qrow, 2 * kc + h);
+            else a = lds_frag_planes<T>(qs_t + (32 * qs + qrow) * RSQ + 16 * kc + 8 * h, Cfg::TILEQ);
             s[qs] = mma(a, kfrag(kc), s[qs]);
           }
           if (kc < KCV) {
-            const Frag<T> g = SWZ ? lds_frag_swz128<T>(dos_t, 32 * qs + qrow, 2 * kc + h)
-                                  : lds_frag<T>(dos_t + (32 * qs + qrow) * RSO + 16 * kc + 8 * h);
+            Frag<T> g;
+            if constexpr (SWZ) g = lds_frag_swz128<T>(dos_t, 32 * qs + qrow, 2 * kc + h);
+            else g = lds_frag_planes<T>(dos_t + (32 * qs + qrow) * RSO + 16 * kc + 8 * h, Cfg::TILEO);
             dp[qs] = mma(g, vf[kc], dp[qs]);
           }
         }
@@ -560,18 +560,19 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
           const int key_rel = (int)(key - q0);  // key minus the tile's first query
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            if (key_rel > 32 * qs + permuted_row(r, h)) s[qs][r] = -INFINITY;
+            if (key_rel > 32 * qs + permuted_row(r, h)) {
+              s[qs][r] = -INFINITY;
+              if (sizeof(T) == 4) dp[qs][r] = 0.0f;
+            }
         }
       }
       auto col_o = [&](int qc, int dt) __attribute__((always_inline)) {
         if constexpr (SWZ) return lds_col_frag_swz128<T>(dos_t, 16 * qc, 32 * dt, lane);
-        else if constexpr (sizeof(T) == 2) return lds_col_frag<T>(dos_t, RSO, 16 * qc, 32 * dt, lane);
-        else return lds_col_frag_f32(reinterpret_cast<const float*>(dos_t), RSO, 16 * qc, 32 * dt, lane);
+        else return lds_col_frag_planes<T>(dos_t, Cfg::TILEO, RSO, 16 * qc, 32 * dt, lane);
       };
       auto col_q = [&](int qc, int dt) __attribute__((always_inline)) {
         if constexpr (SWZ) return lds_col_frag_swz128<T>(qs_t, 16 * qc, 32 * dt, lane);
-        else if constexpr (sizeof(T) == 2) return lds_col_frag<T>(qs_t, RSQ, 16 * qc, 32 * dt, lane);
-        else return lds_col_frag_f32(reinterpret_cast<const float*>(qs_t), RSQ, 16 * qc, 32 * dt, lane);
+        else return lds_col_frag_planes<T>(qs_t, Cfg::TILEQ, RSQ, 16 * qc, 32 * dt, lane);
       };
       constexpr int NDTM = NDT > NDTV ? NDT : NDTV;
       if constexpr (ILV) {
@@ -680,7 +681,8 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
       } else {
         if (has_next) load_stage(BoolC<false>{}, q_begin + (int64_t)(it + 1) * Cfg::BQ);
         compute(it);
-        if (has_next) store_stage(BoolC<false>{}, (it + 1) & 1);
+        if (NBUF == 1) __syncthreads();
+        if (has_next) store_stage(BoolC<false>{}, (it + 1) & (NBUF - 1));
       }
       __syncthreads();
     }
@@ -1204,19 +1206,35 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pp_kernel(BwdParams p) {
 #ifndef MEA_T128_DQ_SWZ
 #define MEA_T128_DQ_SWZ 1
 #endif
+// LDS of a dQ workgroup: K and V tiles of BKW * SW keys.
+template <typename T, int D, int DV, int QT, int BKW, int SW>
+struct DqTile {
+  static constexpr int NP = Planes<T>::NP;
+  static constexpr int STAGE_BYTES = BKW * SW * (D + DV + 16) * NP * 2;
+  static constexpr int RED_BYTES = (4 / SW) * (SW - 1) * QT * (D / 32) * 16 * 64 * 4;
+  static constexpr int nbuf(int occ) { return 2 * STAGE_BYTES <= 160 * 1024 / occ ? 2 : 1; }
+  static constexpr int lds_bytes(int occ) {
+    const int b = nbuf(occ) * STAGE_BYTES;
+    return b > RED_BYTES ? b : RED_BYTES;
+  }
+};
+
 // One workgroup's share of dQ: logical tile w of p.n_qtiles * p.bh.  SW waves
 // share 32 QT queries and split the keys between them, BKW keys each of every
 // staged tile.
-template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, bool CAUSAL>
+template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, int OCC, bool CAUSAL>
 __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, bool light_first) {
   constexpr int NT = 256;
   constexpr int QWAVES = 4 / SW;
   constexpr int BQ = QWAVES * 32 * QT;  // queries per workgroup
   constexpr int BK = BKW * SW;          // keys per staged tile
-  constexpr int E = sizeof(T);
-  constexpr int RSK = D + 16 / E, RSV = DV + 16 / E;  // LDS row strides (elements), 16 B pad
-  constexpr int TILEK = BK * RSK, TILEV = BK * RSV;
-  constexpr int CPRK = D * E / 16, CPRV = DV * E / 16;
+  constexpr int E = 2;                          // bytes of an LDS element
+  constexpr int NP = Planes<T>::NP;
+  using LE = typename Planes<T>::E;
+  constexpr int NBUF = DqTile<T, D, DV, QT, BKW, SW>::nbuf(OCC);
+  constexpr int RSK = D + 8, RSV = DV + 8;      // LDS row strides (elements), 16 B pad
+  constexpr int TILEK = BK * RSK, TILEV = BK * RSV;  // one plane
+  constexpr int CPRK = D / 8, CPRV = DV / 8;    // 8-element chunks per row
   constexpr int CHUNKS = BK * (CPRK + CPRV);
   constexpr int CPT = CHUNKS / NT;
   static_assert(CHUNKS % NT == 0, "tile must split evenly");
@@ -1229,11 +1247,12 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, bool light_fi
   // chunks are XOR-swizzled by the row (swz128), which keeps the row and the
   // transposing reads free of bank conflicts and frees the staging registers.
   constexpr bool SWZ = MEA_T128_DQ_SWZ && sizeof(T) == 2 && D == 128 && DV == 128 && BKW == 32;
-  constexpr int TK = SWZ ? BK * D : TILEK, TV = SWZ ? BK * DV : TILEV;  // tile sizes (elements)
+  constexpr int TK = SWZ ? BK * D : NP * TILEK, TV = SWZ ? BK * DV : NP * TILEV;  // tile sizes (elements)
+  static_assert(!SWZ || NBUF == 2, "asynchronous copies need two stages");
   constexpr int DQ_AHEAD = MEA_T128_DQ_AHEAD;
 
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* smem = reinterpret_cast<T*>(smem_raw);
+  LE* smem = reinterpret_cast<LE*>(smem_raw);
 
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
@@ -1264,21 +1283,11 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, bool light_fi
     const bool valid = query < p.n_q;
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
-      if (valid) {
-        qf[t][kc] = *reinterpret_cast<const Frag<T>*>(qg + query * p.sq.r + 16 * kc + 8 * h);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) qf[t][kc][e] = (T)0.0f;
-      }
+      qf[t][kc] = valid ? ld_frag_as<T, T>(qg + query * p.sq.r + 16 * kc + 8 * h) : zero_frag<T>();
     }
 #pragma unroll
     for (int kc = 0; kc < KCV; ++kc) {
-      if (valid) {
-        gf[t][kc] = ld_frag_as<T, TO>(dog + query * p.sdo.r + 16 * kc + 8 * h);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) gf[t][kc][e] = (T)0.0f;
-      }
+      gf[t][kc] = valid ? ld_frag_as<T, TO>(dog + query * p.sdo.r + 16 * kc + 8 * h) : zero_frag<T>();
     }
     s_init[t] = valid ? row_init(query, true) : -INFINITY;
     dp_init[t] = valid ? row_init(query, false) : 0.0f;
@@ -1305,9 +1314,9 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, bool light_fi
   // (PF = 1): with the causal early exit of a tile the compiler moved the
   // two sets to scratch memory and the kernel ran 5x slower.
   constexpr int PF = 1;
-  u32x4 stage_a[CPT], stage_b[CPT];
+  Chunk8<T> stage_a[CPT], stage_b[CPT];
   auto load_stage = [&](auto set_tag, int64_t k0) __attribute__((always_inline)) {
-    u32x4 (&stage)[CPT] = decltype(set_tag)::value ? stage_b : stage_a;
+    Chunk8<T> (&stage)[CPT] = decltype(set_tag)::value ? stage_b : stage_a;
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
       // The K tile's BK * CPRK chunks, then the V tile's.
@@ -1317,13 +1326,13 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, bool light_fi
       const int cpr = is_v ? CPRV : CPRK;
       const int row = rem / cpr, col = rem % cpr;
       const int64_t kr = k0 + row;
-      const T* src = (is_v ? vg + kr * p.sv.r : kg + kr * p.sk.r) + col * (16 / E);
-      stage[i] = kr < p.n_k ? ld16(src) : u32x4{0u, 0u, 0u, 0u};
+      const T* src = (is_v ? vg + kr * p.sv.r : kg + kr * p.sk.r) + 8 * col;
+      stage[i] = kr < p.n_k ? ld_chunk8<T, T>(src) : zero_chunk8<T>();
     }
   };
   auto store_stage = [&](auto set_tag, int buf) __attribute__((always_inline)) {
-    const u32x4 (&stage)[CPT] = decltype(set_tag)::value ? stage_b : stage_a;
-    T* base = smem + buf * (TILEK + TILEV);
+    const Chunk8<T> (&stage)[CPT] = decltype(set_tag)::value ? stage_b : stage_a;
+    LE* base = smem + buf * (TK + TV);
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
       const int chunk = tid + i * NT;
@@ -1331,7 +1340,7 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, bool light_fi
       const int rem = is_v ? chunk - BK * CPRK : chunk;
       const int cpr = is_v ? CPRV : CPRK;
       const int row = rem / cpr, col = rem % cpr;
-      st16(base + (is_v ? TILEK + row * RSV : row * RSK) + col * (16 / E), stage[i]);
+      st_chunk8<T>(base + (is_v ? TK + row * RSV : row * RSK) + 8 * col, is_v ? TILEV : TILEK, stage[i]);
     }
   };
 
@@ -1394,8 +1403,8 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, bool light_fi
   auto tile = [&](auto mask_tag, int it) {
     constexpr bool MASK = decltype(mask_tag)::value;
     const int64_t k0 = (int64_t)it * BK + ksub;
-    const T* ks = smem + (it & 1) * (TK + TV) + ksub * (SWZ ? D : RSK);
-    const T* vs = smem + (it & 1) * (TK + TV) + TK + ksub * (SWZ ? DV : RSV);
+    const LE* ks = smem + (it & (NBUF - 1)) * (TK + TV) + ksub * (SWZ ? D : RSK);
+    const LE* vs = smem + (it & (NBUF - 1)) * (TK + TV) + TK + ksub * (SWZ ? DV : RSV);
     if (MASK && CAUSAL && k0 > qw + 32 * QT - 1) return;  // all keys after this wave's queries
     f32x16 s[NKT][QT], dp[NKT][QT];
 #pragma unroll
@@ -1434,14 +1443,16 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, bool light_fi
 #pragma unroll
       for (int kt = 0; kt < NKT; ++kt) {
         if (kc < KC) {
-          const Frag<T> a = SWZ ? lds_frag_swz128<T>(ks, 32 * kt + krow, 2 * kc + h)
-                                : lds_frag<T>(ks + (32 * kt + krow) * RSK + 16 * kc + 8 * h);
+          Frag<T> a;
+          if constexpr (SWZ) a = lds_frag_swz128<T>(ks, 32 * kt + krow, 2 * kc + h);
+          else a = lds_frag_planes<T>(ks + (32 * kt + krow) * RSK + 16 * kc + 8 * h, TILEK);
 #pragma unroll
           for (int t = 0; t < QT; ++t) s[kt][t] = mma(a, qf[t][kc], s[kt][t]);
         }
         if (kc < KCV) {
-          const Frag<T> b = SWZ ? lds_frag_swz128<T>(vs, 32 * kt + krow, 2 * kc + h)
-                                : lds_frag<T>(vs + (32 * kt + krow) * RSV + 16 * kc + 8 * h);
+          Frag<T> b;
+          if constexpr (SWZ) b = lds_frag_swz128<T>(vs, 32 * kt + krow, 2 * kc + h);
+          else b = lds_frag_planes<T>(vs + (32 * kt + krow) * RSV + 16 * kc + 8 * h, TILEV);
 #pragma unroll
           for (int t = 0; t < QT; ++t) dp[kt][t] = mma(b, gf[t][kc], dp[kt][t]);
         }
@@ -1482,10 +1493,8 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, bool light_fi
         Frag<T> a;
         if constexpr (SWZ) {
           a = lds_col_frag_swz128<T>(ks, 16 * pc, 32 * dt, lane);
-        } else if constexpr (sizeof(T) == 2) {
-          a = lds_col_frag<T>(ks, RSK, 16 * pc, 32 * dt, lane);
         } else {
-          a = lds_col_frag_f32(reinterpret_cast<const float*>(ks), RSK, 16 * pc, 32 * dt, lane);
+          a = lds_col_frag_planes<T>(ks, TILEK, RSK, 16 * pc, 32 * dt, lane);
         }
 #pragma unroll
         for (int t = 0; t < QT; ++t) acc[t][dt] = mma(a, b[t], acc[t][dt]);
@@ -1511,7 +1520,8 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, bool light_fi
       if (it + 1 < n_tiles) load_stage(BoolC<false>{}, (int64_t)(it + 1) * BK);
     }
     tile(mask_tag, it);
-    if (it + 1 < n_tiles) store_stage(BoolC<PF == 2 && !ODD>{}, (it + 1) & 1);
+    if (NBUF == 1) __syncthreads();
+    if (it + 1 < n_tiles) store_stage(BoolC<PF == 2 && !ODD>{}, (it + 1) & (NBUF - 1));
     __syncthreads();
   };
   auto run = [&](auto mask_tag, int it) __attribute__((always_inline)) {
@@ -2060,7 +2070,7 @@ void attn_bwd_kernel(BwdParams p) {
   if constexpr (PARTS & 1)
     if (b < n_kv) dkdv_tile<T, TO, D, DV, S::QS, SW, OCC, CAUSAL>(p, xcd_remap(b, n_kv));
   if constexpr (PARTS & 2)
-    if (b >= n_kv) dq_tile<T, TO, D, DV, S::QT, S::BK, SW, CAUSAL>(p, xcd_remap(b - n_kv, (int)gridDim.x - n_kv), light_first);
+    if (b >= n_kv) dq_tile<T, TO, D, DV, S::QT, S::BK, SW, OCC, CAUSAL>(p, xcd_remap(b - n_kv, (int)gridDim.x - n_kv), light_first);
 }
 
 template <typename T, typename TO, int D, int DV, int SW, int PARTS, bool CAUSAL>
@@ -2068,17 +2078,14 @@ static hipError_t launch_bwd_parts(const BwdParams& p, hipStream_t stream) {
   using S = BwdShape<T, (D > DV ? D : DV), SW>;
   using Dk = DkdvTile<T, D, DV, S::QS, SW>;
   constexpr int OCC = PARTS == 2 ? S::Q_OCC : S::KV_OCC;
-  constexpr int E = (int)sizeof(T);
   BwdParams q = p;
   q.n_ktiles = (int)((p.n_k + Dk::BKG - 1) / Dk::BKG);
   constexpr int BQ = 128 * S::QT / SW;
   q.n_qtiles = (int)((p.n_q + BQ - 1) / BQ);
   constexpr int kv_lds = Dk::lds_bytes(OCC, __is_same(T, TO));
-  constexpr int dq_stage = 2 * S::BK * SW * (D + DV + 2 * 16 / E) * E;
-  constexpr int dq_red = (4 / SW) * (SW - 1) * S::QT * (D / 32) * 16 * 64 * 4;
-  constexpr int dq_lds = dq_stage > dq_red ? dq_stage : dq_red;
+  constexpr int dq_lds = DqTile<T, D, DV, S::QT, S::BK, SW>::lds_bytes(OCC);
   const int lds = !(PARTS & 1) || !p.dk ? dq_lds : (!(PARTS & 2) || !p.dq || kv_lds > dq_lds ? kv_lds : dq_lds);
-  static_assert(kv_lds <= 160 * 1024 && dq_lds <= 160 * 1024, "LDS");
+  static_assert(kv_lds <= 160 * 1024 / OCC && dq_lds <= 160 * 1024 / OCC, "LDS");
   const int64_t grid = ((PARTS & 1) && p.dk ? (int64_t)q.n_ktiles * p.bh : 0) +
                        ((PARTS & 2) && p.dq ? (int64_t)q.n_qtiles * p.bh : 0);
   if (grid == 0) return hipSuccess;
@@ -2119,7 +2126,7 @@ static hipError_t launch_bwd_kernels(BwdParams p, bool pp, hipStream_t stream) {
                              dim3((unsigned)((int64_t)p.n_qtiles * p.bh)), dim3(qpp::NW * 64), args, 0, stream);
     }
   }
-  switch (bwd_stream_waves(CAUSAL, D > DV ? D : DV, p.n_q, p.n_k, p.bh)) {
+  switch (bwd_stream_waves(sizeof(T) == 2, CAUSAL, D > DV ? D : DV, p.n_q, p.n_k, p.bh)) {
     case 4:
       if constexpr (D == 64 && DV == 64) return launch_bwd_sw<T, TO, D, DV, 4, CAUSAL>(p, stream);
     case 2: return launch_bwd_sw<T, TO, D, DV, 2, CAUSAL>(p, stream);

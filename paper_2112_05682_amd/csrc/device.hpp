@@ -8,8 +8,8 @@
 //   B fragment: lane holds B[k = 8h + s][col c], s = 0..7;
 //   C tile    : lane holds C[row 8*(r/4) + 4h + r%4][col c], r = 0..15.
 // A "fragment" is always 8 consecutive k values, so a 16-wide k chunk is one
-// 32x32x16 MFMA for 16-bit types and eight 32x32x2 MFMAs for float32 (MFMA s
-// consumes element s of both fragments, i.e. the k pair {s, 8 + s}).
+// 32x32x16 MFMA for 16-bit types.  float32 operands are three bf16 parts whose
+// sum is the value (Split3), and a chunk is six bf16 MFMAs.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -30,7 +30,13 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 template <typename T> struct FragT;
 template <> struct FragT<__bf16> { typedef bf16x8 type; typedef bf16x4 half; };
 template <> struct FragT<_Float16> { typedef f16x8 type; typedef f16x4 half; };
-template <> struct FragT<float> { typedef f32x8 type; typedef f32x4 half; };
+// Eight float32 values as bf16 parts: hi + mid + lo, each the rounding of what
+// the parts before it leave (the differences are exact in float32, so the sum
+// is the value: 8 + 8 + 8 significant bits).
+struct Split3 {
+  bf16x8 p[3];
+};
+template <> struct FragT<float> { typedef Split3 type; typedef f32x4 half; };
 template <typename T> using Frag = typename FragT<T>::type;
 
 // C += A * B over a 16-wide k chunk.
@@ -40,11 +46,50 @@ __device__ __forceinline__ f32x16 mma(const bf16x8& a, const bf16x8& b, const f3
 __device__ __forceinline__ f32x16 mma(const f16x8& a, const f16x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ f32x16 mma(const f32x8& a, const f32x8& b, f32x16 c) {
-#pragma unroll
-  for (int s = 0; s < 8; ++s) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], c, 0, 0, 0);
-  return c;
+// float32: the six products of parts down to 2^-16 of the first, smallest
+// first; the three left out are below 2^-24 of it.  Six bf16 MFMAs take 192
+// cycles where eight 32x32x2 float32 MFMAs take 512, and round less often:
+// relative error of dot products of N(0, 1) vectors against float64, float32
+// MFMAs / these, 1.5e-7 / 1.1e-7 over 64 terms, 5.9e-7 / 5.1e-7 over 1024,
+// 1.7e-6 / 1.4e-6 over 8192.
+__device__ __forceinline__ f32x16 mma(const Split3& a, const Split3& b, f32x16 c) {
+  c = mma(a.p[0], b.p[2], c);
+  c = mma(a.p[2], b.p[0], c);
+  c = mma(a.p[1], b.p[1], c);
+  c = mma(a.p[0], b.p[1], c);
+  c = mma(a.p[1], b.p[0], c);
+  return mma(a.p[0], b.p[0], c);
 }
+
+// The parts of eight float32 values.  RAW values (read from memory) may be
+// infinite or above the largest bf16: hi and mid are held to the bf16 range,
+// so that an infinity ends up in lo alone and its products keep their sign.
+template <bool RAW>
+__device__ __forceinline__ Split3 split8(const float* x) {
+  constexpr float kMax = 0x1.fep127f;  // largest finite bf16
+  Split3 s;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const __bf16 hi = (__bf16)(RAW ? __builtin_amdgcn_fmed3f(x[e], -kMax, kMax) : x[e]);
+    const float r1 = x[e] - (float)hi;
+    const __bf16 mid = (__bf16)(RAW ? __builtin_amdgcn_fmed3f(r1, -kMax, kMax) : r1);
+    s.p[0][e] = hi;
+    s.p[1][e] = mid;
+    s.p[2][e] = (__bf16)(r1 - (float)mid);
+  }
+  return s;
+}
+
+// How a tile of T lies in LDS: NP planes of 16-bit elements E (float32: the
+// three parts).
+template <typename T> struct Planes {
+  typedef T E;
+  static constexpr int NP = 1;
+};
+template <> struct Planes<float> {
+  typedef __bf16 E;
+  static constexpr int NP = 3;
+};
 
 // Row of the 32x32 C tile held in register r by a lane of half h.
 __device__ __forceinline__ constexpr int c_row(int r, int h) { return 8 * (r / 4) + 4 * h + (r % 4); }
@@ -60,7 +105,7 @@ __device__ __forceinline__ constexpr int perm32(int i) {
 }
 __device__ __forceinline__ constexpr int permuted_row(int r, int h) { return 16 * (r / 8) + 8 * h + (r % 8); }
 
-// Eight consecutive elements from LDS (16 B for 16-bit types, 32 B for float).
+// Eight consecutive 16-bit elements from LDS.
 template <typename T>
 __device__ __forceinline__ Frag<T> lds_frag(const T* p) {
   return *reinterpret_cast<const Frag<T>*>(p);
@@ -96,13 +141,25 @@ __device__ __forceinline__ Frag<T> lds_col_frag(const T* tile, int rs, int row0,
   return __builtin_bit_cast(Frag<T>, r);
 }
 
-// Float32 column fragment: eight scalar reads.
-__device__ __forceinline__ f32x8 lds_col_frag_f32(const float* tile, int rs, int row0, int col0, int lane) {
-  const int h = lane >> 5, c = lane & 31;
-  f32x8 r;
-#pragma unroll
-  for (int s = 0; s < 8; ++s) r[s] = tile[(row0 + 8 * h + s) * rs + col0 + c];
-  return r;
+// The same fragments of a tile of T, whose planes are `plane` elements apart.
+template <typename T>
+__device__ __forceinline__ Frag<T> lds_frag_planes(const typename Planes<T>::E* p, int plane) {
+  if constexpr (sizeof(T) == 2) {
+    return lds_frag<T>(p);
+  } else {
+    return Split3{{lds_frag<__bf16>(p), lds_frag<__bf16>(p + plane), lds_frag<__bf16>(p + 2 * plane)}};
+  }
+}
+template <typename T>
+__device__ __forceinline__ Frag<T> lds_col_frag_planes(const typename Planes<T>::E* tile, int plane, int rs, int row0,
+                                                       int col0, int lane) {
+  if constexpr (sizeof(T) == 2) {
+    return lds_col_frag<T>(tile, rs, row0, col0, lane);
+  } else {
+    return Split3{{lds_col_frag<__bf16>(tile, rs, row0, col0, lane),
+                   lds_col_frag<__bf16>(tile + plane, rs, row0, col0, lane),
+                   lds_col_frag<__bf16>(tile + 2 * plane, rs, row0, col0, lane)}};
+  }
 }
 
 // Value of x in the lane of the other half (l ^ 32), via v_permlane32_swap:
@@ -225,10 +282,19 @@ __device__ __forceinline__ void copy_to_lds16_sb(const void* base, unsigned voff
 // Convert eight float32 values to a fragment of T (round to nearest even).
 template <typename T>
 __device__ __forceinline__ Frag<T> to_frag(const float* x) {
-  Frag<T> r;
+  if constexpr (sizeof(T) == 4) {
+    return split8<false>(x);
+  } else {
+    Frag<T> r;
 #pragma unroll
-  for (int s = 0; s < 8; ++s) r[s] = (T)x[s];
-  return r;
+    for (int s = 0; s < 8; ++s) r[s] = (T)x[s];
+    return r;
+  }
+}
+template <typename T>
+__device__ __forceinline__ Frag<T> zero_frag() {
+  const float z[8] = {};
+  return to_frag<T>(z);
 }
 
 // Two float32 values rounded to T (nearest even) and packed low, high.
@@ -283,37 +349,65 @@ __device__ __forceinline__ void store_out4(TO* og, TO* lo, const float (&x)[4]) 
 __device__ __forceinline__ u32x4 ld16(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
 __device__ __forceinline__ void st16(void* p, u32x4 v) { *reinterpret_cast<u32x4*>(p) = v; }
 
-// 16/sizeof(T) consecutive elements read from an array of TO and returned in
-// T format (TO is T, or float for a 16-bit T: 32 bytes read and rounded).
+// Eight consecutive elements of a TO array on their way to an LDS tile of T
+// (TO is T, or float for a 16-bit T: rounded), and their store into its planes.
+template <typename T> struct Chunk8T { typedef u32x4 type; };
+template <> struct Chunk8T<float> { typedef f32x8 type; };
+template <typename T> using Chunk8 = typename Chunk8T<T>::type;
+template <typename T>
+__device__ __forceinline__ Chunk8<T> zero_chunk8() {
+  return Chunk8<T>{};
+}
 template <typename T, typename TO>
-__device__ __forceinline__ u32x4 ld_chunk_as(const TO* src) {
-  if constexpr (__is_same(T, TO)) {
+__device__ __forceinline__ Chunk8<T> ld_chunk8(const TO* src) {
+  if constexpr (sizeof(T) == 2 && __is_same(T, TO)) {
     return ld16(src);
   } else {
-    static_assert(__is_same(TO, float) && sizeof(T) == 2, "float -> 16-bit only");
     const f32x4 a = *reinterpret_cast<const f32x4*>(src);
     const f32x4 b = *reinterpret_cast<const f32x4*>(src + 4);
-    Frag<T> f;
+    if constexpr (sizeof(T) == 4) {
+      return f32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    } else {
+      Frag<T> f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      f[e] = (T)a[e];
-      f[4 + e] = (T)b[e];
+      for (int e = 0; e < 4; ++e) {
+        f[e] = (T)a[e];
+        f[4 + e] = (T)b[e];
+      }
+      return __builtin_bit_cast(u32x4, f);
     }
-    return __builtin_bit_cast(u32x4, f);
+  }
+}
+template <typename T>
+__device__ __forceinline__ void st_chunk8(typename Planes<T>::E* dst, int plane, const Chunk8<T>& c) {
+  if constexpr (sizeof(T) == 2) {
+    st16(dst, c);
+  } else {
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = c[e];
+    const Split3 s = split8<true>(x);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) st16(dst + i * plane, __builtin_bit_cast(u32x4, s.p[i]));
   }
 }
 
 // Eight consecutive elements of a TO array as a fragment of T.
 template <typename T, typename TO>
 __device__ __forceinline__ Frag<T> ld_frag_as(const TO* src) {
-  if constexpr (__is_same(T, TO)) {
+  if constexpr (sizeof(T) == 2 && __is_same(T, TO)) {
     return *reinterpret_cast<const Frag<T>*>(src);
   } else {
-    const f32x8 x = *reinterpret_cast<const f32x8*>(src);
-    Frag<T> f;
+    float x[8];
+    const f32x4 a = *reinterpret_cast<const f32x4*>(src);
+    const f32x4 b = *reinterpret_cast<const f32x4*>(src + 4);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = (T)x[e];
-    return f;
+    for (int e = 0; e < 4; ++e) {
+      x[e] = a[e];
+      x[4 + e] = b[e];
+    }
+    if constexpr (sizeof(T) == 4) return split8<true>(x);
+    else return to_frag<T>(x);
   }
 }
 

@@ -14,7 +14,9 @@
 //   - a workgroup is 4 waves; each wave owns QT tiles of 32 queries, so a
 //     workgroup covers BQ = 128*QT queries;
 //   - K and V tiles of BK keys are staged through double-buffered LDS with
-//     coalesced 16-byte global loads; Q stays in registers;
+//     coalesced 16-byte global loads; Q stays in registers; float32 tiles are
+//     split into their bf16 parts on the way (see Split3), once for the
+//     workgroup;
 //   - scores are computed transposed, S^T = K Q^T, so that each lane owns one
 //     query (column) and its softmax state is a per-lane scalar; the key rows
 //     are read in the perm32 order so that the S^T tile, exponentiated and
@@ -33,30 +35,34 @@ template <bool B> struct BoolC { static constexpr bool value = B; };
 template <int I> struct IntC { static constexpr int value = I; };
 
 // D: head dimension of q and k; DV: of v and o.
-template <typename T, int D, int DV, int QT, int BK>
+template <typename T, int D, int DV, int QT, int BK, int OCC>
 struct FwdTile {
   static constexpr int NW = 4;
   static constexpr int NT = NW * 64;
   static constexpr int BQ = NW * QT * 32;
-  static constexpr int E = sizeof(T);
-  // LDS row strides (elements).  K rows (read 16 bytes per lane, 16 rows
-  // per 16 lanes) carry a 16-byte pad: each row starts 4 banks after the
+  static constexpr int NP = Planes<T>::NP;
+  // LDS row strides (16-bit elements).  K rows (read 16 bytes per lane, 16
+  // rows per 16 lanes) carry a 16-byte pad: each row starts 4 banks after the
   // previous one, so the 16 rows cover all 64 banks.  V rows are read by the
   // transposing read, 4 consecutive rows x 64 bytes per 32 lanes: a 64-byte pad
   // (16 banks) keeps those 4 rows in disjoint banks (a 16-byte pad made them
-  // overlap 4 ways).  float32 V is read by scalar loads and keeps 16 bytes.
-  static constexpr int RSK = D + 16 / E;
-  static constexpr int RSV = DV + (E == 2 ? 64 : 16) / E;
-  static constexpr int TILEK = BK * RSK;         // elements of the K tile
-  static constexpr int TILEV = BK * RSV;         // elements of the V tile
-  static constexpr int STAGE = TILEK + TILEV;    // one K/V stage
-  static constexpr int CPRK = D * E / 16;        // 16-byte chunks per row
-  static constexpr int CPRV = DV * E / 16;
+  // overlap 4 ways).
+  static constexpr int RSK = D + 8;
+  static constexpr int RSV = DV + 32;
+  static constexpr int TILEK = BK * RSK;         // elements of one K plane
+  static constexpr int TILEV = BK * RSV;         // elements of one V plane
+  static constexpr int STAGE = NP * (TILEK + TILEV);  // one K/V stage
+  static constexpr int CPRK = D / 8;             // 8-element chunks per row
+  static constexpr int CPRV = DV / 8;
   static constexpr int CHUNKS = BK * (CPRK + CPRV);  // K and V chunks per stage
   static constexpr int CPT = CHUNKS / NT;        // chunks per thread per stage
-  static constexpr int LDS_BYTES = 2 * STAGE * E;  // double-buffered K and V
+  // Two stages where OCC workgroups' fit the CU's 160 KiB, else one (float32
+  // at 128 features).
+  static constexpr int NBUF = 2 * STAGE * 2 * OCC <= 160 * 1024 ? 2 : 1;
+  static constexpr int LDS_BYTES = NBUF * STAGE * 2;
   static_assert(CHUNKS % NT == 0, "tile must split evenly over the workgroup");
   static_assert(BK % 32 == 0 && D % 32 == 0 && DV % 32 == 0, "tile shapes are multiples of 32");
+  static_assert(LDS_BYTES * OCC <= 160 * 1024, "LDS");
 };
 
 #ifndef MEA_FWD_ILV
@@ -64,7 +70,8 @@ struct FwdTile {
 #endif
 template <typename T, typename TO, int D, int DV, int QT, int BK, int OCC, bool CAUSAL>
 __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
-  using Cfg = FwdTile<T, D, DV, QT, BK>;
+  using Cfg = FwdTile<T, D, DV, QT, BK, OCC>;
+  using LE = typename Planes<T>::E;  // element of an LDS tile
   constexpr int RSK = Cfg::RSK, RSV = Cfg::RSV;
   constexpr int KC = D / 16;    // 16-wide k chunks of the QK^T contraction
   constexpr int NKT = BK / 32;  // 32-key sub-tiles per tile
@@ -73,7 +80,7 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
   constexpr bool ILV = MEA_FWD_ILV && sizeof(T) == 2 && NDT == 2;
 
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* smem = reinterpret_cast<T*>(smem_raw);
+  LE* smem = reinterpret_cast<LE*>(smem_raw);
 
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
@@ -107,14 +114,8 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
   for (int t = 0; t < QT; ++t) {
     const int64_t row = qw + 32 * t + c;
 #pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
-      if (row < p.n_q) {
-        qf[t][kc] = *reinterpret_cast<const Frag<T>*>(qg + row * p.sq.r + 16 * kc + 8 * h);
-      } else {
-#pragma unroll
-        for (int s = 0; s < 8; ++s) qf[t][kc][s] = (T)0.0f;
-      }
-    }
+    for (int kc = 0; kc < KC; ++kc)
+      qf[t][kc] = row < p.n_q ? ld_frag_as<T, T>(qg + row * p.sq.r + 16 * kc + 8 * h) : zero_frag<T>();
   }
 
   wait_global_loads();
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
   }
 
   // ---- global -> register staging of one K/V stage (zero rows past n_k).
-  u32x4 stage[Cfg::CPT];
+  Chunk8<T> stage[Cfg::CPT];
   // Chunk i of a stage: the K tile's BK * CPRK chunks, then the V tile's.
   auto load_stage = [&](int64_t k0) {
 #pragma unroll
@@ -148,12 +149,11 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
       const int row = rem / cpr, col = rem % cpr;
       const int64_t key = k0 + row;
       const T* src = is_v ? vg + key * p.sv.r : kg + key * p.sk.r;
-      src += col * (16 / Cfg::E);
-      stage[i] = key < p.n_k ? ld16(src) : u32x4{0u, 0u, 0u, 0u};
+      stage[i] = key < p.n_k ? ld_chunk8<T, T>(src + 8 * col) : zero_chunk8<T>();
     }
   };
   auto store_stage = [&](int buf) {
-    T* base = smem + buf * Cfg::STAGE;
+    LE* base = smem + buf * Cfg::STAGE;
 #pragma unroll
     for (int i = 0; i < Cfg::CPT; ++i) {
       const int chunk = tid + i * Cfg::NT;
@@ -161,7 +161,8 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
       const int rem = is_v ? chunk - BK * Cfg::CPRK : chunk;
       const int cpr = is_v ? Cfg::CPRV : Cfg::CPRK;
       const int row = rem / cpr, col = rem % cpr;
-      st16(base + (is_v ? Cfg::TILEK + row * RSV : row * RSK) + col * (16 / Cfg::E), stage[i]);
+      st_chunk8<T>(base + (is_v ? Cfg::NP * Cfg::TILEK + row * RSV : row * RSK) + 8 * col,
+                   is_v ? Cfg::TILEV : Cfg::TILEK, stage[i]);
     }
   };
 
@@ -185,8 +186,8 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
   auto tile = [&](auto mask_tag, int it) {
     constexpr bool MASK = decltype(mask_tag)::value;
     const int64_t k0 = kb + (int64_t)it * BK;
-    const T* ks = smem + (it & 1) * Cfg::STAGE;
-    const T* vs = ks + Cfg::TILEK;
+    const LE* ks = smem + (it & (Cfg::NBUF - 1)) * Cfg::STAGE;
+    const LE* vs = ks + Cfg::NP * Cfg::TILEK;
     // A wave whose queries all precede the tile's first key has nothing to do.
     if (MASK && CAUSAL && k0 > qw + QT * 32 - 1) return;
 
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
     for (int kc = 0; kc < KC; ++kc) {
 #pragma unroll
       for (int kt = 0; kt < NKT; ++kt) {
-        const Frag<T> a = lds_frag<T>(ks + (32 * kt + krow) * RSK + 16 * kc + 8 * h);
+        const Frag<T> a = lds_frag_planes<T>(ks + (32 * kt + krow) * RSK + 16 * kc + 8 * h, Cfg::TILEK);
 #pragma unroll
         for (int t = 0; t < QT; ++t) s[kt][t] = mma(a, qf[t][kc], s[kt][t]);
       }
@@ -265,8 +266,7 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
       }
     }
     auto col_v = [&](int pc, int dt) __attribute__((always_inline)) {
-      if constexpr (sizeof(T) == 2) return lds_col_frag<T>(vs, RSV, 16 * pc, 32 * dt, lane);
-      else return lds_col_frag_f32(reinterpret_cast<const float*>(vs), RSV, 16 * pc, 32 * dt, lane);
+      return lds_col_frag_planes<T>(vs, Cfg::TILEV, RSV, 16 * pc, 32 * dt, lane);
     };
     if constexpr (ILV) {
       // O^T += V^T P^T chunk by chunk; the weights of 16-key chunk pc + 1 are
@@ -307,25 +307,47 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
       return;
     }
     // O^T += V^T P^T; each V^T fragment feeds every query sub-tile.
+    // float32: a tile's products are summed apart and added to the numerator
+    // once, so that it rounds once per tile and not 6 NPC times (relative error
+    // of o over 60000 keys 1.2e-6 without this; 1.1e-6 with float32 MFMAs).
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt) {
+      if constexpr (sizeof(T) == 4) {
 #pragma unroll
-      for (int pc = 0; pc < NPC; ++pc) {
-        const Frag<T> a = col_v(pc, dt);
+        for (int t = 0; t < QT; ++t) {
+          f32x16 sum = {};
 #pragma unroll
-        for (int t = 0; t < QT; ++t) acc[t][dt] = mma(a, pf[t][pc], acc[t][dt]);
+          for (int pc = 0; pc < NPC; ++pc) {
+            const Frag<T> a = col_v(pc, dt);
+            sum = mma(a, pf[t][pc], sum);
+          }
+          acc[t][dt] += sum;
+        }
+      } else {
+#pragma unroll
+        for (int pc = 0; pc < NPC; ++pc) {
+          const Frag<T> a = col_v(pc, dt);
+#pragma unroll
+          for (int t = 0; t < QT; ++t) acc[t][dt] = mma(a, pf[t][pc], acc[t][dt]);
+        }
       }
     }
   };
 
-  // Double-buffered pipeline: the next tile is fetched into registers while
-  // the current one is computed, then written to the other LDS stage.  Masked
+  // Pipeline: the next tile is fetched into registers while the current one is
+  // computed, then written to the other LDS stage.  With one stage the tile is
+  // fetched when every wave is done with it: the fetch then holds no registers
+  // through the tile, and the CU's other workgroup computes meanwhile.  Masked
   // tiles (ragged tail, causal diagonal) run in a separate second loop.
   auto step = [&](auto mask_tag, int it) {
     const bool has_next = it + 1 < n_tiles;
-    if (has_next) load_stage(kb + (int64_t)(it + 1) * BK);
+    if (Cfg::NBUF == 2 && has_next) load_stage(kb + (int64_t)(it + 1) * BK);
     tile(mask_tag, it);
-    if (has_next) store_stage((it + 1) & 1);
+    if (Cfg::NBUF == 1) {
+      __syncthreads();
+      if (has_next) load_stage(kb + (int64_t)(it + 1) * BK);
+    }
+    if (has_next) store_stage((it + 1) & (Cfg::NBUF - 1));
     __syncthreads();
   };
   if (n_tiles > 0) {
@@ -1126,7 +1148,7 @@ static hipError_t launch_combine(const FwdParams& p, hipStream_t stream) {
 
 template <typename T, typename TO, int D, int DV, int QT, int BK, int OCC, bool CAUSAL>
 static hipError_t launch_fwd_impl(const FwdParams& p, hipStream_t stream) {
-  using Cfg = FwdTile<T, D, DV, QT, BK>;
+  using Cfg = FwdTile<T, D, DV, QT, BK, OCC>;
   auto kern = attn_fwd_kernel<T, TO, D, DV, QT, BK, OCC, CAUSAL>;
   // The plan's query tiles must be this kernel's (4 waves x QT x 32 queries).
   if (p.n_qtiles != (p.n_q + 128 * QT - 1) / (128 * QT)) return hipErrorInvalidValue;
@@ -1179,8 +1201,9 @@ static hipError_t launch_fwd_dt(const FwdParams& p, bool causal, hipStream_t str
 template <typename T, typename TO, int D, int DV>
 static hipError_t launch_fwd_dv(const FwdParams& p, bool causal, hipStream_t stream) {
   using S = FwdShape<T, 128>;
-  return causal ? launch_fwd_impl<T, TO, D, DV, S::QT, S::BK, S::OCC, true>(p, stream)
-                : launch_fwd_impl<T, TO, D, DV, S::QT, S::BK, S::OCC, false>(p, stream);
+  constexpr int OCC = 2;  // float32 too: a 64-wide side leaves the registers
+  return causal ? launch_fwd_impl<T, TO, D, DV, S::QT, S::BK, OCC, true>(p, stream)
+                : launch_fwd_impl<T, TO, D, DV, S::QT, S::BK, OCC, false>(p, stream);
 }
 template <typename T, typename TO>
 static hipError_t launch_fwd_dv_pair(const FwdParams& p, int d, bool causal, hipStream_t stream) {

@@ -183,11 +183,18 @@ inline int64_t bwd_tiles128(int64_t n_q, int64_t n_k, int64_t bh) {
 // 1x8x4096 (512) 109 / 90 / 118, 4x8x1024 (512) 37 / 42 / 53, 2x8x4096 (1024)
 // 171 / 172 / 230; d = 128 2x8x512 (128) 32 / 25, causal 1x8x2000 (256) 101 /
 // 68, unmasked 87 / 101, causal 1x12x2000 (384) 109 / 111.
-inline int bwd_stream_waves(bool causal, int dmax, int64_t n_q, int64_t n_k, int64_t bh) {
+// float32 fits one workgroup per CU whatever the shares, and its passes are
+// longer: 64 rows a share pay up to the same counts, 32 rows (one stage of 128
+// rows) only where a quarter of the CUs would be busy.  1 / 2 / 4 waves, d = 64
+// 1x4x1000 (64 tiles) 168 / 66 / 47, 1x8x1000 (128) 168 / 69 / 81, 2x8x1000
+// (256) 172 / 113 / 159, 3x8x1000 (384) 175 / 176; causal 1x8x1000 (128) 172 /
+// 68 / 57, 4x8x1000 (512) 179 / 167, 1x8x4000 (512) 630 / 430 / 598; d = 128
+// 1x8x1000 (128) 188 / 133, 2x8x1000 (256) 193 / 244, causal 191 / 204.
+inline int bwd_stream_waves(bool is16, bool causal, int dmax, int64_t n_q, int64_t n_k, int64_t bh) {
   int64_t tiles = bwd_tiles128(n_q, n_k, bh);
-  if (causal && n_q > 1024) tiles /= 2;
+  if (causal && (n_q > 1024 || (!is16 && dmax == 64))) tiles /= 2;
   if (dmax == 128) return tiles <= 128 ? 2 : 1;
-  return tiles <= 128 ? 4 : (tiles <= 256 ? 2 : 1);
+  return tiles <= (is16 ? 128 : 64) ? 4 : (tiles <= 256 ? 2 : 1);
 }
 // Whether dK/dV and dQ run in one launch (4-wave kernels, one wave per
 // column): faster wherever the two grids can fill each other's gaps, on large
@@ -285,7 +292,10 @@ template <> struct FwdShape<_Float16, 64> {
 };
 template <> struct FwdShape<_Float16, 128> { static constexpr int QT = 1, BK = 64, BQ = MEA_T128_FWD_BQ, OCC = 2; };
 template <> struct FwdShape<float, 64> { static constexpr int QT = 1, BK = 32, BQ = 128, OCC = 2; };
-template <> struct FwdShape<float, 128> { static constexpr int QT = 1, BK = 32, BQ = 128, OCC = 2; };
+// float32, d = d_v = 128: two workgroups per CU would need 256 registers for
+// 160 of operands' parts and sums and spill (0.90 ms at 2x8x3000 unmasked
+// against 0.60 ms with one per CU; 0.77 ms with float32 MFMAs).
+template <> struct FwdShape<float, 128> { static constexpr int QT = 1, BK = 32, BQ = 128, OCC = 1; };
 
 // dtype codes follow mea_dtype: 0 = f32, 1 = f16, 2 = bf16.
 // out_f32: o (and, in the backward, do) are float32 instead of the input dtype.
