@@ -90,6 +90,7 @@ struct FwdPlan {
   int bq, bk;
   int64_t n_qtiles;
   int n_splits;
+  int stream_waves;  // see FwdParams
   int64_t keys_per_split;
   size_t workspace;
 };
@@ -110,9 +111,6 @@ void fwd_tiles(int dtype, int64_t d, int64_t dv, bool causal, int64_t n_q, int64
   }
 }
 
-// Grid plan.  The chip has 256 CUs; when the query tiles alone give too few
-// workgroups, the keys are split so that each split's summary is combined
-// afterwards (Section 4 combine).
 // Decode plan: one wave per key range; ranges of at least 4 key tiles, about
 // MEA_DECODE_TARGET_WG workgroups in all, at most 1024 ranges per (batch,
 // head).  1024 workgroups are one round of four per CU (the LDS ring allows
@@ -125,6 +123,7 @@ FwdPlan plan_decode(const mea_problem* p) {
   pl.bq = 64;
   pl.bk = mea::fwd_decode_tile((int)p->d);
   pl.n_qtiles = 1;
+  pl.stream_waves = 0;
   const int64_t bh = p->batch * p->heads;
   const int64_t n_keys = p->causal && p->n_k > p->n_q ? p->n_q : p->n_k;
   const int64_t k_tiles = (n_keys + pl.bk - 1) / pl.bk;
@@ -144,29 +143,22 @@ FwdPlan plan_decode(const mea_problem* p) {
   return pl;
 }
 
+// The chip has 256 CUs; when the query tiles alone give too few workgroups,
+// several waves share a tile's queries, or the keys are split and each split's
+// summary is combined afterwards (Section 4 combine): fwd_grid.
 FwdPlan plan_fwd(const mea_problem* p) {
   if (mea::fwd_uses_decode((int)p->dtype, (int)p->d, (int)dv_of(p), p->n_q)) return plan_decode(p);
   FwdPlan pl;
   const int64_t bh = p->batch * p->heads;
   fwd_tiles(p->dtype, p->d, dv_of(p), p->causal != 0, p->n_q, bh, &pl.bq, &pl.bk);
   pl.n_qtiles = (p->n_q + pl.bq - 1) / pl.bq;
+  const mea::FwdGrid g =
+      mea::fwd_grid(p->dtype != MEA_F32, p->causal != 0, (int)p->d, (int)dv_of(p), p->n_q, p->n_k, bh);
+  pl.stream_waves = g.waves;
+  if (g.waves) pl.bk = mea::fwd_stream_tile(p->dtype != MEA_F32, g.waves);
   const int64_t k_tiles = (p->n_k + pl.bk - 1) / pl.bk;
-  const int64_t base = bh * pl.n_qtiles;
-  int64_t splits = 1;
-  // Whole rounds of workgroups: 1024 (four per CU) for the kernels that fit
-  // one or two per CU, one round of MEA_T64_FWD_OCC per CU for the 16-bit
-  // d = 64 4-wave kernel (three: 768 workgroups measured 2-12 % faster than
-  // 1024 on 65-256 queries against 32768-262144 keys, and the same as 1536).
-  const bool four_wave64 = pl.bq == 128 && p->dtype != MEA_F32 && p->d == 64 && dv_of(p) == 64;
-  const int64_t kTargetWorkgroups = four_wave64 ? 256 * MEA_T64_FWD_OCC : 1024;
-  const int64_t kMinTilesPerSplit = 16;
-  if (base < 512 && k_tiles >= 2 * kMinTilesPerSplit) {
-    splits = (kTargetWorkgroups + base - 1) / base;
-    const int64_t max_splits = k_tiles / kMinTilesPerSplit;
-    if (splits > max_splits) splits = max_splits;
-    if (splits > 64) splits = 64;
-    if (splits < 1) splits = 1;
-  }
+  int64_t splits = g.ranges;
+  if (splits > k_tiles) splits = k_tiles;
   const int64_t tiles_per_split = (k_tiles + splits - 1) / splits;
   pl.keys_per_split = tiles_per_split * pl.bk;
   pl.n_splits = (int)((p->n_k + pl.keys_per_split - 1) / pl.keys_per_split);
@@ -327,6 +319,7 @@ mea_status mea_attention_fwd(const mea_problem* p, const void* q, const void* k,
   fp.bh = (int)(p->batch * p->heads);
   fp.n_qtiles = (int)pl.n_qtiles;
   fp.n_splits = pl.n_splits;
+  fp.stream_waves = pl.stream_waves;
   fp.scale = p->scale;
   fp.scale_log2 = p->scale * kLog2e;
   fp.heads = (int)p->heads;
@@ -355,7 +348,12 @@ mea_status mea_attention_fwd(const mea_problem* p, const void* q, const void* k,
       fp.part2_l = fp.part2_m + r2;
     }
   }
-  const int64_t grid = (int64_t)fp.n_qtiles * fp.bh * fp.n_splits;
+  const int64_t q_tiles =
+      pl.stream_waves ? (p->n_q + 128 / pl.stream_waves - 1) / (128 / pl.stream_waves) : (int64_t)fp.n_qtiles;
+  const int64_t grid = q_tiles * fp.bh * fp.n_splits;
+  if (p->causal)
+    fp.tile_order = mea::causal_tile_order((int64_t)fp.bh * p->n_k * (p->d + dv_of(p)) * (int64_t)elem_size(p->dtype),
+                                           grid, pl.stream_waves != 0);
   if (grid >= ((int64_t)1 << 31)) return MEA_ERR_INVALID_ARG;
   const hipError_t e = mea::launch_fwd(fp, p->dtype, (int)p->d, (int)dv_of(p), p->causal != 0,
                                        p->out_f32 != 0, stream);
@@ -423,6 +421,9 @@ mea_status bwd_launch(const mea_problem* p, const void* q, const void* k, const 
   bp.n_q = p->n_q;
   bp.n_k = p->n_k;
   bp.bh = (int)(p->batch * p->heads);
+  if (p->causal)
+    bp.tile_order = mea::causal_tile_order(
+        (int64_t)bp.bh * p->n_k * (p->d + dv_of(p)) * (int64_t)elem_size(p->dtype), 0, false);
   bp.scale = p->scale;
   bp.scale_log2 = p->scale * kLog2e;
   bp.heads = (int)p->heads;

@@ -254,9 +254,9 @@ __device__ __forceinline__ Frag<T> lds_col_frag_swz128(const T* tile, int row0, 
 #ifndef MEA_DKDV_ILV
 #define MEA_DKDV_ILV 1
 #endif
-// One workgroup's share of dK and dV: logical tile w of p.n_ktiles * p.bh.
+// One workgroup's share of dK and dV: workgroup w of n_wg = p.n_ktiles * p.bh.
 template <typename T, typename TO, int D, int DV, int QS, int SW, int OCC, bool CAUSAL>
-__device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
+__device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
   using Cfg = DkdvTile<T, D, DV, QS, SW>;
   using LE = typename Planes<T>::E;  // element of an LDS tile
   constexpr int KWAVES = 4 / SW;  // 32-key columns of the workgroup
@@ -271,9 +271,10 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w) {
   const int wave = tid >> 6, lane = tid & 63;
   const int h = lane >> 5, c = lane & 31;
 
-  const int wave_k = wave % KWAVES, wave_q = wave / KWAVES;
-  const int kt_idx = w % p.n_ktiles;  // heaviest (earliest keys) first under causal
-  const int bh = bh_of_group(w / p.n_ktiles, p.bh, p.heads);
+  const int wave_k = SW > 1 ? wave % KWAVES : wave, wave_q = SW > 1 ? wave / KWAVES : 0;
+  const TileItem item = tile_item(w, n_wg, p.n_ktiles, CAUSAL ? p.tile_order : 0);
+  const int kt_idx = item.tile;  // heaviest (earliest keys) first under causal
+  const int bh = bh_of_group(item.group, p.bh, p.heads);
   const int64_t k0 = (int64_t)kt_idx * Cfg::BKG;
   const int64_t kw = k0 + 32 * wave_k;
   const int qsub = 32 * QS * wave_q;  // first query of this wave in a staged tile
@@ -789,9 +790,9 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_pp_kernel(BwdParams p) {
   const int lane = tid & 63;
   const int h = lane >> 5, c = lane & 31;
 
-  const int w = xcd_remap(blockIdx.x, gridDim.x);
-  const int kt_idx = w % p.n_ktiles;
-  const int bh = bh_of_group(w / p.n_ktiles, p.bh, p.heads);
+  const TileItem item = tile_item(blockIdx.x, gridDim.x, p.n_ktiles, CAUSAL ? p.tile_order : 0);
+  const int kt_idx = item.tile;
+  const int bh = bh_of_group(item.group, p.bh, p.heads);
   const int64_t k0 = (int64_t)kt_idx * BKG;
   const int64_t kw = k0 + 32 * wave;
   const int64_t key = kw + c;
@@ -1219,11 +1220,11 @@ struct DqTile {
   }
 };
 
-// One workgroup's share of dQ: logical tile w of p.n_qtiles * p.bh.  SW waves
+// One workgroup's share of dQ: workgroup w of n_wg = p.n_qtiles * p.bh.  SW waves
 // share 32 QT queries and split the keys between them, BKW keys each of every
 // staged tile.
 template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, int OCC, bool CAUSAL>
-__device__ __forceinline__ void dq_tile(const BwdParams& p, int w, bool light_first) {
+__device__ __forceinline__ void dq_tile(const BwdParams& p, int w, int n_wg, bool light_first) {
   constexpr int NT = 256;
   constexpr int QWAVES = 4 / SW;
   constexpr int BQ = QWAVES * 32 * QT;  // queries per workgroup
@@ -1258,10 +1259,11 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, bool light_fi
   const int wave = tid >> 6, lane = tid & 63;
   const int h = lane >> 5, c = lane & 31;
 
-  const int wave_q = wave % QWAVES, wave_k = wave / QWAVES;
+  const int wave_q = SW > 1 ? wave % QWAVES : wave, wave_k = SW > 1 ? wave / QWAVES : 0;
   const int ksub = BKW * wave_k;  // first key of this wave in a staged tile
-  const int qt_idx = w % p.n_qtiles;
-  const int bh = bh_of_group(w / p.n_qtiles, p.bh, p.heads);
+  const TileItem item = tile_item(w, n_wg, p.n_qtiles, CAUSAL ? p.tile_order : 0);
+  const int qt_idx = item.tile;
+  const int bh = bh_of_group(item.group, p.bh, p.heads);
   const int qtile = CAUSAL && !light_first ? (p.n_qtiles - 1 - qt_idx) : qt_idx;
   const int64_t q0 = (int64_t)qtile * BQ;
   const int64_t qw = q0 + 32 * QT * wave_q;  // first query of this wave
@@ -1605,9 +1607,9 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_pp_kernel(BwdParams p) {
   const int lane = tid & 63;
   const int h = lane >> 5, c = lane & 31;
 
-  const int w = xcd_remap(blockIdx.x, gridDim.x);
-  const int qt_idx = w % p.n_qtiles;
-  const int bh = bh_of_group(w / p.n_qtiles, p.bh, p.heads);
+  const TileItem item = tile_item(blockIdx.x, gridDim.x, p.n_qtiles, CAUSAL ? p.tile_order : 0);
+  const int qt_idx = item.tile;
+  const int bh = bh_of_group(item.group, p.bh, p.heads);
   const int qtile = CAUSAL ? (p.n_qtiles - 1 - qt_idx) : qt_idx;  // heaviest first
   const int64_t q0 = (int64_t)qtile * BQG;
   const int64_t qw = q0 + 32 * wave;  // first query of this wave
@@ -2068,9 +2070,9 @@ void attn_bwd_kernel(BwdParams p) {
   // go first.
   const bool light_first = n_kv > 0 && (int)gridDim.x <= 256 * OCC;
   if constexpr (PARTS & 1)
-    if (b < n_kv) dkdv_tile<T, TO, D, DV, S::QS, SW, OCC, CAUSAL>(p, xcd_remap(b, n_kv));
+    if (b < n_kv) dkdv_tile<T, TO, D, DV, S::QS, SW, OCC, CAUSAL>(p, b, n_kv);
   if constexpr (PARTS & 2)
-    if (b >= n_kv) dq_tile<T, TO, D, DV, S::QT, S::BK, SW, OCC, CAUSAL>(p, xcd_remap(b - n_kv, (int)gridDim.x - n_kv), light_first);
+    if (b >= n_kv) dq_tile<T, TO, D, DV, S::QT, S::BK, SW, OCC, CAUSAL>(p, b - n_kv, (int)gridDim.x - n_kv, light_first);
 }
 
 template <typename T, typename TO, int D, int DV, int SW, int PARTS, bool CAUSAL>

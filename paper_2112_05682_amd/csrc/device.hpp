@@ -420,6 +420,32 @@ __device__ __forceinline__ int xcd_remap(int w, int n) {
   return x * per + (x < rem ? x : rem) + i;
 }
 
+// Orders of a causal grid's tiles (TileOrder of the kernels' arguments).  Head
+// major: a (batch, head)'s tiles one after the other, on one XCD.  Tile major:
+// the heaviest tile of every (batch, head) first, then the next, dealt to the
+// XCDs in turn (where the number of (batch, head) pairs is a multiple of 8
+// each stays on one XCD all the same).  Folded, for a grid that is resident at
+// once: as tile major, but an XCD gives each of its 32 CUs one workgroup, then
+// the next, and every other such round is reversed, so that the heaviest tiles
+// share a CU with the lightest.
+//
+// Item (tile rank, group) of workgroup w of n; n = n_tiles * groups.
+// Bijective in every order.
+struct TileItem {
+  int tile, group;
+};
+__device__ __forceinline__ TileItem tile_item(int w, int n, int n_tiles, int order) {
+  if (order == 0) {
+    const int g = xcd_remap(w, n);
+    return {g % n_tiles, g / n_tiles};
+  }
+  const int x = w & 7, i = w >> 3, n_x = (n - x + 7) >> 3;
+  const int r0 = i & ~31, cnt = n_x - r0 < 32 ? n_x - r0 : 32;
+  const int j = order == 2 && (r0 & 32) ? r0 + cnt - 1 - (i - r0) : i;
+  const int g = 8 * j + x, groups = n / n_tiles;
+  return {g / groups, g % groups};
+}
+
 // (batch, head) index of the g-th (batch, head) pair in the order the grid
 // enumerates them: batch fastest, then head.  Consecutive logical tiles (and so
 // each XCD's contiguous range of them) then mix all batches, which keeps the

@@ -35,11 +35,14 @@ template <bool B> struct BoolC { static constexpr bool value = B; };
 template <int I> struct IntC { static constexpr int value = I; };
 
 // D: head dimension of q and k; DV: of v and o.
-template <typename T, int D, int DV, int QT, int BK, int OCC>
+// SW: waves that share 32 QT queries and split the keys, BKW of every staged
+// tile each.
+template <typename T, int D, int DV, int QT, int BKW, int SW, int OCC>
 struct FwdTile {
   static constexpr int NW = 4;
   static constexpr int NT = NW * 64;
-  static constexpr int BQ = NW * QT * 32;
+  static constexpr int BQ = NW / SW * QT * 32;
+  static constexpr int BK = BKW * SW;
   static constexpr int NP = Planes<T>::NP;
   // LDS row strides (16-bit elements).  K rows (read 16 bytes per lane, 16
   // rows per 16 lanes) carry a 16-byte pad: each row starts 4 banks after the
@@ -59,7 +62,11 @@ struct FwdTile {
   // Two stages where OCC workgroups' fit the CU's 160 KiB, else one (float32
   // at 128 features).
   static constexpr int NBUF = 2 * STAGE * 2 * OCC <= 160 * 1024 ? 2 : 1;
-  static constexpr int LDS_BYTES = NBUF * STAGE * 2;
+  // SW > 1: the waves' maxima and denominators, then their numerators, pass
+  // through the stages' space after the last tile.
+  static constexpr int ML_BYTES = 2 * NW * QT * 32 * 4;
+  static constexpr int RED_BYTES = SW > 1 ? ML_BYTES + NW / SW * QT * (DV / 32) * (SW - 1) * 4096 : 0;
+  static constexpr int LDS_BYTES = NBUF * STAGE * 2 > RED_BYTES ? NBUF * STAGE * 2 : RED_BYTES;
   static_assert(CHUNKS % NT == 0, "tile must split evenly over the workgroup");
   static_assert(BK % 32 == 0 && D % 32 == 0 && DV % 32 == 0, "tile shapes are multiples of 32");
   static_assert(LDS_BYTES * OCC <= 160 * 1024, "LDS");
@@ -68,14 +75,15 @@ struct FwdTile {
 #ifndef MEA_FWD_ILV
 #define MEA_FWD_ILV 1
 #endif
-template <typename T, typename TO, int D, int DV, int QT, int BK, int OCC, bool CAUSAL>
+template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, int OCC, bool CAUSAL>
 __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
-  using Cfg = FwdTile<T, D, DV, QT, BK, OCC>;
+  using Cfg = FwdTile<T, D, DV, QT, BKW, SW, OCC>;
+  constexpr int BK = Cfg::BK, QWAVES = 4 / SW;
   using LE = typename Planes<T>::E;  // element of an LDS tile
   constexpr int RSK = Cfg::RSK, RSV = Cfg::RSV;
   constexpr int KC = D / 16;    // 16-wide k chunks of the QK^T contraction
-  constexpr int NKT = BK / 32;  // 32-key sub-tiles per tile
-  constexpr int NPC = BK / 16;  // 16-key chunks of the PV contraction
+  constexpr int NKT = BKW / 32;  // 32-key sub-tiles per tile and wave
+  constexpr int NPC = BKW / 16;  // 16-key chunks of the PV contraction
   constexpr int NDT = DV / 32;  // 32-row tiles of O^T
   constexpr bool ILV = MEA_FWD_ILV && sizeof(T) == 2 && NDT == 2;
 
@@ -87,14 +95,15 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
   const int h = lane >> 5, c = lane & 31;
 
   // ---- workgroup -> (split, bh, query tile); heaviest causal tiles first.
-  const int w = xcd_remap(blockIdx.x, gridDim.x);
-  const int qt_idx = w % p.n_qtiles;
-  const int rest = w / p.n_qtiles;
+  const TileItem item = tile_item(blockIdx.x, gridDim.x, p.n_qtiles, CAUSAL ? p.tile_order : 0);
+  const int qt_idx = item.tile, rest = item.group;
   const int bh = bh_of_group(rest % p.bh, p.bh, p.heads);
   const int split = rest / p.bh;
   const int qtile = CAUSAL ? (p.n_qtiles - 1 - qt_idx) : qt_idx;
   const int64_t q0 = (int64_t)qtile * Cfg::BQ;
-  const int64_t qw = q0 + (int64_t)wave * QT * 32;  // first query of this wave
+  const int wave_q = SW > 1 ? wave % QWAVES : wave, wave_k = SW > 1 ? wave / QWAVES : 0;
+  const int64_t qw = q0 + (int64_t)wave_q * QT * 32;  // first query of this wave
+  const int ksub = BKW * wave_k;                      // its first key in a staged tile
 
   const T* __restrict__ qg = static_cast<const T*>(p.q) + head_base(p.sq, bh, p.heads);
   const T* __restrict__ kg = static_cast<const T*>(p.k) + head_base(p.sk, bh, p.heads);
@@ -136,33 +145,43 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
     l_run[t] = 0.0f;
   }
 
-  // ---- global -> register staging of one K/V stage (zero rows past n_k).
-  Chunk8<T> stage[Cfg::CPT];
+  // ---- global -> LDS staging of one K/V stage (zero rows past n_k).  EARLY:
+  // through registers that hold the next tile while one is computed; else
+  // between the tiles (wide stages have no registers for that, float32 ones
+  // at 128 features neither).
+  constexpr bool EARLY = Cfg::CPT * (int)sizeof(Chunk8<T>) <= 128 &&
+                         (Cfg::NBUF == 2 || sizeof(T) == 2 || (D == 64 && DV == 64));
+  Chunk8<T> stage[EARLY ? Cfg::CPT : 1];
   // Chunk i of a stage: the K tile's BK * CPRK chunks, then the V tile's.
-  auto load_stage = [&](int64_t k0) {
-#pragma unroll
-    for (int i = 0; i < Cfg::CPT; ++i) {
-      const int chunk = tid + i * Cfg::NT;
-      const bool is_v = chunk >= BK * Cfg::CPRK;
-      const int rem = is_v ? chunk - BK * Cfg::CPRK : chunk;
-      const int cpr = is_v ? Cfg::CPRV : Cfg::CPRK;
-      const int row = rem / cpr, col = rem % cpr;
-      const int64_t key = k0 + row;
-      const T* src = is_v ? vg + key * p.sv.r : kg + key * p.sk.r;
-      stage[i] = key < p.n_k ? ld_chunk8<T, T>(src + 8 * col) : zero_chunk8<T>();
-    }
+  auto load_chunk = [&](int i, int64_t k0) __attribute__((always_inline)) {
+    const int chunk = tid + i * Cfg::NT;
+    const bool is_v = chunk >= BK * Cfg::CPRK;
+    const int rem = is_v ? chunk - BK * Cfg::CPRK : chunk;
+    const int cpr = is_v ? Cfg::CPRV : Cfg::CPRK;
+    const int row = rem / cpr, col = rem % cpr;
+    const int64_t key = k0 + row;
+    const T* src = is_v ? vg + key * p.sv.r : kg + key * p.sk.r;
+    return key < p.n_k ? ld_chunk8<T, T>(src + 8 * col) : zero_chunk8<T>();
   };
-  auto store_stage = [&](int buf) {
-    LE* base = smem + buf * Cfg::STAGE;
+  auto store_chunk = [&](int i, int buf, const Chunk8<T>& x) __attribute__((always_inline)) {
+    const int chunk = tid + i * Cfg::NT;
+    const bool is_v = chunk >= BK * Cfg::CPRK;
+    const int rem = is_v ? chunk - BK * Cfg::CPRK : chunk;
+    const int cpr = is_v ? Cfg::CPRV : Cfg::CPRK;
+    const int row = rem / cpr, col = rem % cpr;
+    st_chunk8<T>(smem + buf * Cfg::STAGE + (is_v ? Cfg::NP * Cfg::TILEK + row * RSV : row * RSK) + 8 * col,
+                 is_v ? Cfg::TILEV : Cfg::TILEK, x);
+  };
+  auto load_stage = [&](int64_t k0) __attribute__((always_inline)) {
+    if constexpr (EARLY)
+#pragma unroll
+      for (int i = 0; i < Cfg::CPT; ++i) stage[i] = load_chunk(i, k0);
+  };
+  auto store_stage = [&](int64_t k0, int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < Cfg::CPT; ++i) {
-      const int chunk = tid + i * Cfg::NT;
-      const bool is_v = chunk >= BK * Cfg::CPRK;
-      const int rem = is_v ? chunk - BK * Cfg::CPRK : chunk;
-      const int cpr = is_v ? Cfg::CPRV : Cfg::CPRK;
-      const int row = rem / cpr, col = rem % cpr;
-      st_chunk8<T>(base + (is_v ? Cfg::NP * Cfg::TILEK + row * RSV : row * RSK) + 8 * col,
-                   is_v ? Cfg::TILEV : Cfg::TILEK, stage[i]);
+      if constexpr (EARLY) store_chunk(i, buf, stage[i]);
+      else store_chunk(i, buf, load_chunk(i, k0));
     }
   };
 
@@ -185,9 +204,9 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
   // lazily raised reference maximum, O^T += V^T P^T.
   auto tile = [&](auto mask_tag, int it) {
     constexpr bool MASK = decltype(mask_tag)::value;
-    const int64_t k0 = kb + (int64_t)it * BK;
-    const LE* ks = smem + (it & (Cfg::NBUF - 1)) * Cfg::STAGE;
-    const LE* vs = ks + Cfg::NP * Cfg::TILEK;
+    const int64_t k0 = kb + (int64_t)it * BK + ksub;
+    const LE* ks = smem + (it & (Cfg::NBUF - 1)) * Cfg::STAGE + ksub * RSK;
+    const LE* vs = smem + (it & (Cfg::NBUF - 1)) * Cfg::STAGE + Cfg::NP * Cfg::TILEK + ksub * RSV;
     // A wave whose queries all precede the tile's first key has nothing to do.
     if (MASK && CAUSAL && k0 > qw + QT * 32 - 1) return;
 
@@ -211,8 +230,8 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
     if constexpr (MASK) {
       // Tile-relative 32-bit bounds: key k0 + x is valid iff x < key_lim and,
       // under the causal mask, visible to query qw + 32t + c iff x <= q_rel + 32t.
-      const int key_lim = (int)(n_k - k0 < BK ? n_k - k0 : BK);
-      const int q_rel = CAUSAL ? (int)(qw - k0) + c : BK;
+      const int key_lim = (int)(n_k - k0 < BKW ? n_k - k0 : BKW);
+      const int q_rel = CAUSAL ? (int)(qw - k0) + c : BKW;
 #pragma unroll
       for (int t = 0; t < QT; ++t) {
         const int lim_c = q_rel + 32 * t + 1;
@@ -335,34 +354,86 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
   };
 
   // Pipeline: the next tile is fetched into registers while the current one is
-  // computed, then written to the other LDS stage.  With one stage the tile is
-  // fetched when every wave is done with it: the fetch then holds no registers
-  // through the tile, and the CU's other workgroup computes meanwhile.  Masked
+  // computed, then written to the other LDS stage, or to the only one when
+  // every wave is done with it.  Masked
   // tiles (ragged tail, causal diagonal) run in a separate second loop.
   auto step = [&](auto mask_tag, int it) {
     const bool has_next = it + 1 < n_tiles;
-    if (Cfg::NBUF == 2 && has_next) load_stage(kb + (int64_t)(it + 1) * BK);
+    const int64_t k_next = kb + (int64_t)(it + 1) * BK;
+    if (has_next) load_stage(k_next);
     tile(mask_tag, it);
-    if (Cfg::NBUF == 1) {
-      __syncthreads();
-      if (has_next) load_stage(kb + (int64_t)(it + 1) * BK);
-    }
-    if (has_next) store_stage((it + 1) & (Cfg::NBUF - 1));
+    if (Cfg::NBUF == 1) __syncthreads();
+    if (has_next) store_stage(k_next, (it + 1) & (Cfg::NBUF - 1));
     __syncthreads();
   };
   if (n_tiles > 0) {
     load_stage(kb);
-    store_stage(0);
+    store_stage(kb, 0);
   }
   __syncthreads();
   int it = 0;
   for (; it < n_plain; ++it) step(BoolC<false>{}, it);
   for (; it < n_tiles; ++it) step(BoolC<true>{}, it);
 
+  // ---- SW > 1: one summary of the waves that share the queries (Section 4's
+  // combine): rescale to the common maximum and add, in the order of the
+  // waves.  The wave with wave_k == dt % SW owns 32-feature tile dt, adds the
+  // others' and stores it.
+  float l_sum[QT];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) l_sum[t] = xhalf_sum(l_run[t]);
+  if constexpr (SW > 1) {
+    float* red_m = reinterpret_cast<float*>(smem_raw);  // free after the last tile's barrier
+    float* red_l = red_m + 4 * QT * 32;
+    float* red_o = red_m + Cfg::ML_BYTES / 4 + wave_q * QT * NDT * (SW - 1) * 1024 + lane;
+#pragma unroll
+    for (int t = 0; t < QT; ++t)
+      if (h == 0) {
+        red_m[(wave * QT + t) * 32 + c] = m_ref[t];
+        red_l[(wave * QT + t) * 32 + c] = l_sum[t];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      float m_g = -INFINITY, l_g = 0.0f;
+#pragma unroll
+      for (int y = 0; y < SW; ++y) m_g = fmaxf(m_g, red_m[((wave_q + y * QWAVES) * QT + t) * 32 + c]);
+#pragma unroll
+      for (int y = 0; y < SW; ++y) {
+        const int i = ((wave_q + y * QWAVES) * QT + t) * 32 + c;
+        const float m_y = red_m[i];
+        l_g += m_y == -INFINITY ? 0.0f : fast_exp2(m_y - m_g) * red_l[i];
+      }
+      const float f = m_ref[t] == -INFINITY ? 0.0f : fast_exp2(m_ref[t] - m_g);
+      m_ref[t] = m_g;
+      l_sum[t] = l_g;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][dt][r] *= f;
+        if (dt % SW != wave_k)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            red_o[(((t * NDT + dt) * (SW - 1) + wave_k - (wave_k > dt % SW)) * 16 + r) * 64] = acc[t][dt][r];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < QT; ++t)
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt)
+        if (dt % SW == wave_k)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int y = 0; y < SW - 1; ++y)
+              acc[t][dt][r] += red_o[(((t * NDT + dt) * (SW - 1) + y) * 16 + r) * 64];
+  }
+
   // ---- epilogue.
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
-    const float l_tot = xhalf_sum(l_run[t]);
+    const float l_tot = l_sum[t];
     const int64_t row = qw + 32 * t + c;
     if (row >= p.n_q) continue;
     if (p.n_splits == 1) {
@@ -371,7 +442,8 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
       TO* og = static_cast<TO*>(p.o) + head_base(p.so, bh, p.heads) + row * p.so.r;
       TO* gl = p.o_lo ? static_cast<TO*>(p.o_lo) + ((size_t)bh * p.n_q + row) * DV : nullptr;
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt)
+      for (int dt = 0; dt < NDT; ++dt) {
+        if (SW > 1 && dt % SW != wave_k) continue;
 #pragma unroll
         for (int a4 = 0; a4 < 4; ++a4) {
           float x4[4];
@@ -380,13 +452,15 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
           const int f = 32 * dt + 8 * a4 + 4 * h;
           store_out4<TO>(og + f, gl ? gl + f : nullptr, x4);
         }
-      if (h == 0 && p.lse)
+      }
+      if (h == 0 && wave_k == 0 && p.lse)
         p.lse[(size_t)bh * p.n_q + row] = l_tot > 0.0f ? (m_ref[t] + __log2f(l_tot)) * kLn2 : -INFINITY;
     } else {
       const size_t prow = ((size_t)split * p.bh + bh) * p.n_q + row;
       float* po = p.part_o + prow * DV;
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt)
+      for (int dt = 0; dt < NDT; ++dt) {
+        if (SW > 1 && dt % SW != wave_k) continue;
 #pragma unroll
         for (int a4 = 0; a4 < 4; ++a4) {
           f32x4 v4;
@@ -394,7 +468,8 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
           for (int e = 0; e < 4; ++e) v4[e] = acc[t][dt][4 * a4 + e];
           *reinterpret_cast<f32x4*>(po + 32 * dt + 8 * a4 + 4 * h) = v4;
         }
-      if (h == 0) {
+      }
+      if (h == 0 && wave_k == 0) {
         p.part_m[prow] = m_ref[t];  // log2 units (scaled), -inf if no visible key
         p.part_l[prow] = l_tot;
       }
@@ -497,9 +572,8 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_pp_kernel(FwdParams p) {
   const int lane = tid & 63;
   const int h = lane >> 5, c = lane & 31;
 
-  const int w = xcd_remap(blockIdx.x, gridDim.x);
-  const int qt_idx = w % p.n_qtiles;
-  const int rest = w / p.n_qtiles;
+  const TileItem item = tile_item(blockIdx.x, gridDim.x, p.n_qtiles, CAUSAL ? p.tile_order : 0);
+  const int qt_idx = item.tile, rest = item.group;
   const int bh = bh_of_group(rest % p.bh, p.bh, p.heads);
   const int split = rest / p.bh;
   const int qtile = CAUSAL ? (p.n_qtiles - 1 - qt_idx) : qt_idx;
@@ -1146,14 +1220,15 @@ static hipError_t launch_combine(const FwdParams& p, hipStream_t stream) {
                          dim3((unsigned)((threads + 255) / 256)), dim3(256), args, 0, stream);
 }
 
-template <typename T, typename TO, int D, int DV, int QT, int BK, int OCC, bool CAUSAL>
+template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, int OCC, bool CAUSAL>
 static hipError_t launch_fwd_impl(const FwdParams& p, hipStream_t stream) {
-  using Cfg = FwdTile<T, D, DV, QT, BK, OCC>;
-  auto kern = attn_fwd_kernel<T, TO, D, DV, QT, BK, OCC, CAUSAL>;
-  // The plan's query tiles must be this kernel's (4 waves x QT x 32 queries).
-  if (p.n_qtiles != (p.n_q + 128 * QT - 1) / (128 * QT)) return hipErrorInvalidValue;
-  const int64_t grid = (int64_t)p.n_qtiles * p.bh * p.n_splits;
+  using Cfg = FwdTile<T, D, DV, QT, BKW, SW, OCC>;
+  auto kern = attn_fwd_kernel<T, TO, D, DV, QT, BKW, SW, OCC, CAUSAL>;
   FwdParams pc = p;
+  pc.n_qtiles = (int)((p.n_q + Cfg::BQ - 1) / Cfg::BQ);
+  // The plan must mean this kernel, and a key range must be whole staged tiles.
+  if (p.stream_waves != SW || (p.n_splits > 1 && p.keys_per_split % Cfg::BK)) return hipErrorInvalidValue;
+  const int64_t grid = (int64_t)pc.n_qtiles * p.bh * p.n_splits;
   void* args[] = {&pc};
   hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3((unsigned)grid),
                                  dim3(Cfg::NT), args, Cfg::LDS_BYTES, stream);
@@ -1174,40 +1249,44 @@ static hipError_t launch_fwd_pp(const FwdParams& p, hipStream_t stream) {
   return launch_combine<TO, D>(p, stream);
 }
 
-template <typename T, typename TO, int D>
-static hipError_t launch_fwd_dt(const FwdParams& p, bool causal, hipStream_t stream) {
-  if constexpr (sizeof(T) == 2 && FwdShape<T, D>::BQ == pp::BQ<D>) {
-    // Short or small problems: the 4-wave kernel with 128-query workgroups
-    // (the same choice as the host plan's).
-    if constexpr (D == 64) {
-      if (fwd64_bq(p.n_q, p.bh, causal) == 128)
-        return causal ? launch_fwd_impl<T, TO, 64, 64, 1, FwdShape<T, 64>::BK, MEA_T64_FWD_OCC, true>(p, stream)
-                      : launch_fwd_impl<T, TO, 64, 64, 1, FwdShape<T, 64>::BK, MEA_T64_FWD_OCC, false>(p, stream);
-    } else {
-      using S = FwdShape<T, 128>;
-      if (fwd128_bq(p.n_q, causal) == kFwdBq4wave128)
-        return causal ? launch_fwd_impl<T, TO, 128, 128, S::QT, S::BK, S::OCC, true>(p, stream)
-                      : launch_fwd_impl<T, TO, 128, 128, S::QT, S::BK, S::OCC, false>(p, stream);
-    }
-    return causal ? launch_fwd_pp<T, TO, D, true>(p, stream) : launch_fwd_pp<T, TO, D, false>(p, stream);
+// The 4-wave kernel with SW waves per 32 queries (the plan's choice).
+// Workgroups per CU as their LDS allows: up to 128 staged keys of 64 or 128
+// features, 16-bit or in three parts.
+template <typename T, typename TO, int D, int DV, int SW>
+static hipError_t launch_fwd_sw(const FwdParams& p, bool causal, hipStream_t stream) {
+  constexpr bool WIDE = D == 128 || DV == 128, F32 = sizeof(T) == 4;
+  if constexpr (SW == 1) {
+    constexpr int BK = F32 ? 32 : 64;
+    constexpr int OCC = F32 ? (D == 128 && DV == 128 ? 1 : 2) : (WIDE ? 2 : MEA_T64_FWD_OCC);
+    return causal ? launch_fwd_impl<T, TO, D, DV, 1, BK, 1, OCC, true>(p, stream)
+                  : launch_fwd_impl<T, TO, D, DV, 1, BK, 1, OCC, false>(p, stream);
   } else {
-    constexpr int QT = FwdShape<T, D>::QT, BK = FwdShape<T, D>::BK, OCC = FwdShape<T, D>::OCC;
-    return causal ? launch_fwd_impl<T, TO, D, D, QT, BK, OCC, true>(p, stream)
-                  : launch_fwd_impl<T, TO, D, D, QT, BK, OCC, false>(p, stream);
+    constexpr int OCC = F32 ? (WIDE || SW == 4 ? 1 : 2) : (WIDE ? 2 : (SW == 2 ? 3 : 2));
+    return causal ? launch_fwd_impl<T, TO, D, DV, 1, 32, SW, OCC, true>(p, stream)
+                  : launch_fwd_impl<T, TO, D, DV, 1, 32, SW, OCC, false>(p, stream);
   }
 }
-
-// Value head dimension DV != D: the 4-wave kernel with the d = 128 tile shape.
 template <typename T, typename TO, int D, int DV>
-static hipError_t launch_fwd_dv(const FwdParams& p, bool causal, hipStream_t stream) {
-  using S = FwdShape<T, 128>;
-  constexpr int OCC = 2;  // float32 too: a 64-wide side leaves the registers
-  return causal ? launch_fwd_impl<T, TO, D, DV, S::QT, S::BK, OCC, true>(p, stream)
-                : launch_fwd_impl<T, TO, D, DV, S::QT, S::BK, OCC, false>(p, stream);
+static hipError_t launch_fwd_stream(const FwdParams& p, bool causal, hipStream_t stream) {
+  if constexpr (sizeof(T) == 2 && D == 64 && DV == 64)  // four waves: the only types fwd_grid gives them
+    if (p.stream_waves == 4) return launch_fwd_sw<T, TO, D, DV, 4>(p, causal, stream);
+  if (p.stream_waves == 2) return launch_fwd_sw<T, TO, D, DV, 2>(p, causal, stream);
+  return launch_fwd_sw<T, TO, D, DV, 1>(p, causal, stream);
 }
+
+template <typename T, typename TO, int D>
+static hipError_t launch_fwd_dt(const FwdParams& p, bool causal, hipStream_t stream) {
+  if (p.stream_waves) return launch_fwd_stream<T, TO, D, D>(p, causal, stream);
+  if constexpr (sizeof(T) == 2)
+    return causal ? launch_fwd_pp<T, TO, D, true>(p, stream) : launch_fwd_pp<T, TO, D, false>(p, stream);
+  return hipErrorInvalidValue;  // float32 has the 4-wave kernel only
+}
+
+// Value head dimension DV != D: the 4-wave kernel.
 template <typename T, typename TO>
 static hipError_t launch_fwd_dv_pair(const FwdParams& p, int d, bool causal, hipStream_t stream) {
-  return d == 64 ? launch_fwd_dv<T, TO, 64, 128>(p, causal, stream) : launch_fwd_dv<T, TO, 128, 64>(p, causal, stream);
+  return d == 64 ? launch_fwd_stream<T, TO, 64, 128>(p, causal, stream)
+                 : launch_fwd_stream<T, TO, 128, 64>(p, causal, stream);
 }
 
 template <typename T, int D>

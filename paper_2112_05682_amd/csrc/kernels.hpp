@@ -48,6 +48,10 @@ struct FwdParams {
   int bh;                  // B * H
   int n_qtiles;
   int n_splits;
+  // Waves that share 32 queries in the 4-wave kernel (1, 2 or 4; it derives its
+  // query tiles from this), or 0: the kernel that n_qtiles' tiles belong to.
+  int stream_waves;
+  int tile_order;    // causal problems: 0 head major, 1 tile major, 2 folded (tile_item)
   float scale;       // score scale
   float scale_log2;  // scale * log2(e)
   int heads;         // H (bh = b * H + h)
@@ -109,6 +113,7 @@ struct BwdParams {
   int bh;
   int n_qtiles;  // query tiles of the dQ kernel
   int n_ktiles;  // key tiles of the dK/dV kernel
+  int tile_order;  // causal problems: see FwdParams
   float scale;
   float scale_log2;
   int heads;  // H (bh = b * H + h)
@@ -296,6 +301,104 @@ template <> struct FwdShape<float, 64> { static constexpr int QT = 1, BK = 32, B
 // 160 of operands' parts and sums and spill (0.90 ms at 2x8x3000 unmasked
 // against 0.60 ms with one per CU; 0.77 ms with float32 MFMAs).
 template <> struct FwdShape<float, 128> { static constexpr int QT = 1, BK = 32, BQ = 128, OCC = 1; };
+
+// How a forward that is not decode-shaped fills the chip: the two-group kernel
+// (waves 0; where fwd64_bq or fwd128_bq name it) or the 4-wave kernel with 1, 2
+// or 4 waves per 32 queries, and the key ranges that are combined afterwards.
+//
+// tiles = 128-query tiles of the 4-wave kernel, wgs = the two-group kernel's
+// workgroups (one per CU, so 256 a round).  More waves per 32 queries and more
+// key ranges both make more workgroups of the same work; waves re-read K and V
+// through L2 once more each, ranges cost partial sums in memory and a combine
+// launch (about 5 us), so waves fill the chip at short keys and ranges at long
+// ones.  Measured in us, forward (with its combine), bf16 unless noted,
+// before / with this rule's choice:
+//   two-group kernel, ranges of one round and not 1024 workgroups:
+//     2x16x4096 d = 64 (wgs 256) 4 ranges 213 / 1 range 160, 1x16x4096 d = 128
+//     (256) 172 / 122, 2x16x2048 d = 128 92 / 67, 1x12x4096 d = 64 (96) 87 / 73,
+//     1x1x16384 d = 64 (32) 97 / 82, 1x2x16384 d = 128 (128) 300 / 245
+//   unmasked d = 64: 1x8x1024 (tiles 64) two-group 35 / 4 waves 13, 4x8x1024
+//     (256) 35 / 2 waves 21, 1x1x4096 (32) 40 / 2 waves, 8 ranges 22, 1x4x4096
+//     (128) 47 / 1 wave, 4 ranges 39, 2x16x2048 (512) 55 / 1 wave 50, 16x12x512
+//     (768) 27 / 1 wave 25, 16x16x600 (1280; a 512-query tile is 41 % padding)
+//     58 / 1 wave 45; but 8x16x1024 (1024) 45 / 1 wave 52, 1x24x4096 (768) 117 /
+//     1 wave 134: two-group
+//   causal d = 64: 2x8x1024 (128) 20 / 4 waves 13, 4x8x1024 (256) 20 / 2 waves
+//     16, 1x8x4096 (256) 56 / 2 waves 47; d = 128: 1x32x2047 (512) two-group 91 /
+//     1 wave 62, 1x8x4000 (256) 90 / 2 waves 73, 4x8x1024 (256) 33 / 2 waves 26,
+//     16x16x600 (1280) 68 / 1 wave 63, but 4x32x2047 (2048) 179 / 1 wave 191
+//   d = 128: 1x8x2000 (128) 41 / two-group, 4 ranges 36, 1x1x2000 (16) 32 / 2
+//     waves, 8 ranges 19, 2x8x512 (64) 20 / 2 waves 15
+//   float32: 1x1x256 d = 64 18.5 / 2 waves, 4 ranges 11, 1x8x1000 (64) 37 / 4
+//     ranges 27, 1x1x2000 d = 128 (16) 83 / 2 waves, 8 ranges 37.
+struct FwdGrid {
+  int waves;       // 0: two-group kernel
+  int64_t ranges;  // key ranges wanted (the plan rounds them to whole tiles)
+};
+inline int64_t clamp64(int64_t x, int64_t lo, int64_t hi) { return x < lo ? lo : (x > hi ? hi : x); }
+inline FwdGrid fwd_grid(bool is16, bool causal, int d, int dv, int64_t n_q, int64_t n_k, int64_t bh) {
+  const int64_t tiles = bh * ((n_q + 127) / 128);
+  const bool same = d == dv, wide = d == 128 || dv == 128;
+  const int64_t bq = d == 64 ? 512 : 256, rows = (n_q + bq - 1) / bq * bq, wgs = bh * (rows / bq);
+  const bool two_group = is16 && same && (d == 64 ? fwd64_bq(n_q, bh, causal) : fwd128_bq(n_q, causal)) == bq;
+  const int64_t cap = n_k >= 16384 ? 64 : 8;  // at most 8 ranges but for long keys
+  if (!is16) {
+    const int w = tiles <= 32 ? 2 : 1;
+    const int64_t slots = same && wide ? 256 : 512;
+    return {w, causal && n_k > n_q ? 1 : clamp64(slots / (tiles * w), 1, clamp64(n_k / (w == 2 ? 128 : 256), 1, cap))};
+  }
+  if (causal) {
+    if (same && d == 64) {
+      if (two_group) return {0, 1};
+      return {tiles <= 128 ? 4 : (tiles <= 256 ? 2 : 1), tiles <= 32 ? clamp64(n_k / 256, 1, 4) : 1};
+    }
+    if (same && tiles > 512 && n_q > 1024) return {0, 1};
+    return {tiles <= 256 ? 2 : 1, tiles <= 64 && n_k <= n_q && n_k >= 1024 ? 2 : 1};
+  }
+  // Unmasked.  A last two-group tile that is mostly padding leaves it out.
+  const bool pp = two_group && 4 * n_q >= 3 * rows;
+  if (pp && n_k >= 512 && wgs >= 224) return {0, wgs > 256 && wgs < 512 && n_k >= 16384 ? 4 : 1};
+  const int64_t pp_ranges = clamp64(256 / wgs, 1, clamp64(n_k / 512, 1, 64));
+  if (same && d == 64) {
+    if (tiles >= 512) return {pp && wgs >= 160 && n_k >= 2048 ? 0 : 1, 1};
+    if (tiles >= 256 && n_k < 4096) return {tiles <= 256 ? 2 : 1, 1};
+    if (pp && n_k >= (tiles >= 256 ? 4096 : 8192)) return {0, pp_ranges};
+    if (tiles >= 128)
+      return n_k < 2048 ? FwdGrid{2, 1} : FwdGrid{1, clamp64((n_k >= 16384 ? 768 : 512) / tiles, 1, cap)};
+    if (n_k < 2048) return {4, tiles <= 16 ? clamp64(n_k / 256, 1, 4) : 1};
+    return {2, clamp64(512 / (2 * tiles), 1, clamp64(n_k / 512, 1, cap))};
+  }
+  if (same) {
+    if (pp && n_k >= (tiles >= 128 ? 1024 : 4096)) return {0, pp_ranges};
+    if (tiles >= 384) return {1, 1};
+    const int w = tiles <= 256 && n_k < 4096 ? 2 : 1;
+    return {w, n_k < 1024 && tiles > 16 ? 1 : clamp64(512 / (tiles * w), 1, clamp64(n_k / 256, 1, cap))};
+  }
+  if (tiles > 256) return {1, 1};
+  if (tiles <= 32) return {2, clamp64(512 / (2 * tiles), 1, clamp64(n_k / 512, 1, cap))};
+  if (n_k < 2048 || tiles > 128) return {n_k < 4096 ? 2 : 1, 1};
+  return {1, clamp64(512 / tiles, 1, cap)};
+}
+// Keys of a staged tile of the 4-wave forward with sw waves per 32 queries.
+inline int fwd_stream_tile(bool is16, int sw) { return sw == 1 ? (is16 ? 64 : 32) : 32 * sw; }
+
+// Order of a causal grid's tiles (tile_item in device.hpp).  Tile major starts
+// the heaviest tiles of every head first, so the last workgroups are light
+// ones: 5-30 % on grids of one to a few rounds (us, head / tile major: forward
+// 8x16x2048 d = 64 133 / 112, 4x32x2047 d = 128 208 / 184; backward 8x8x1024 d =
+// 64 70 / 52, 8x8x1024 d = 128 119 / 91, 4x32x4096 d = 64 1128 / 1071; forward +
+// backward 3x5x9000 d = 64 1102 / 836, 2x32x8192 d = 64 2671 / 2493, 8x16x2000
+// d = 128 float32 4531 / 3914).  It touches every head at once, which pays while
+// K and V (and Q and dO, as much again) stay in the 256 MiB last-level cache.
+// Past 128 MiB of K and V it gains little or loses, and the extra traffic costs
+// clock in the kernels after it too: forward + backward 8x32x2047 d = 128 (256
+// MiB) 1575 / 1593, 7x9x10364 d = 64, d_v = 128 (250 MB) 6805 / 7266, 4x32x8192 d =
+// 128 (512 MiB) 9040 / 9510.  Folded evens out a grid that is resident at once
+// (1x32x2047 d = 128 forward 65.5 / 61.9).
+inline int causal_tile_order(int64_t kv_bytes, int64_t grid, bool may_fold) {
+  if (kv_bytes > (int64_t)128 << 20) return 0;
+  return may_fold && grid <= 512 ? 2 : 1;
+}
 
 // dtype codes follow mea_dtype: 0 = f32, 1 = f16, 2 = bf16.
 // out_f32: o (and, in the backward, do) are float32 instead of the input dtype.
