@@ -93,12 +93,13 @@ struct BwdParams {
   // preprocess kernel: s_init = -lse / scale (so that P = 2^(c * (S + s_init)),
   // c = scale * log2 e) and dp_init = -D with D_i = dO_i . O_i (so that
   // dS = P * (dP + dp_init)).  Rows n_q .. n_q_pad - 1 contribute nothing.
-  // The two-group kernels (16-bit inputs and outputs, d = 64) take them as
-  // one 16-byte record per row, eight bf16 values {s_hi, s_mid, s_lo, 0,
-  // d_hi, d_mid, d_lo, 0} whose three parts sum to s_init and dp_init in
-  // float32 (padding rows: s = -2^100, d = 0), so that one bf16 MFMA against
-  // a constant operand puts them into the accumulators; the other kernels
-  // take [B*H, n_q_pad] float32 arrays (padding rows -inf and 0).
+  // Problems that bwd_uses_row_records names (16-bit inputs and outputs,
+  // d = 64) hold them as one 16-byte record per row, eight bf16 values {s_hi,
+  // s_mid, s_lo, 0, d_hi, d_mid, d_lo, 0} whose three parts sum to s_init and
+  // dp_init in float32 (padding rows: s = -2^100, d = 0), so that the two-group
+  // kernels put them into the accumulators with one bf16 MFMA against a
+  // constant operand; the others hold [B*H, n_q_pad] float32 arrays (padding
+  // rows -inf and 0).
   float* s_init;
   float* dp_init;
   uint4* row_rec;
@@ -124,10 +125,10 @@ struct BwdParams {
 // tile the backward kernels stage).
 constexpr int kBwdRowPad = 64;
 
-// Whether the backward runs the two-group kernels, which take the per-row
-// values as 16-byte records; every other backward takes them as two float32
-// arrays.  The host's workspace layout and the kernels' choice both come from
-// this one predicate.  Causal problems of up to MEA_T64_BWD_CAUSAL_SMALL
+// Whether a backward's per-row values are 16-byte records, and with them
+// whether it may run the two-group kernels (bwd_two_group_fills has the last
+// word); every other backward takes two float32 arrays.  The host's workspace
+// layout and the kernels' choice both come from this one predicate.  Causal problems of up to MEA_T64_BWD_CAUSAL_SMALL
 // queries run the 4-wave kernels: measured on causal bf16 d = 64 problems,
 // n = 1024-2048 (128-256 heads) took 5-13 % less time with them; at 3072 the
 // two kinds tie, and from 4096 queries on the two-group kernels take 3-12 %
