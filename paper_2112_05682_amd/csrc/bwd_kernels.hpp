@@ -164,6 +164,18 @@ struct RowInit {
   }
 };
 
+// A row's initial value, added to products of operands that were split times up.
+template <typename T>
+__device__ __forceinline__ float scaled_init(float x, Range<T>& g) {
+  if constexpr (sizeof(T) == 2) {
+    return x;
+  } else {
+    // As large as products of operands up to kRangeTop over 2^8 features.
+    if (x != -INFINITY) g.see(x * (g.up / (kRangeTop * 0x1p8f)));
+    return x * g.up * g.up;
+  }
+}
+
 // ------------------------------------------------------------------- dK, dV
 // D: head dimension of q and k; DV: of v, o and dO; SW: waves that share one
 // 32-key column and split the queries between them.
@@ -255,8 +267,10 @@ __device__ __forceinline__ Frag<T> lds_col_frag_swz128(const T* tile, int row0, 
 #define MEA_DKDV_ILV 1
 #endif
 // One workgroup's share of dK and dV: workgroup w of n_wg = p.n_ktiles * p.bh.
+// Returns whether it is to be done again with up = 1 (float32; nothing is
+// written then).
 template <typename T, typename TO, int D, int DV, int QS, int SW, int OCC, bool CAUSAL>
-__device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
+__device__ __forceinline__ bool dkdv_tile(const BwdParams& p, int w, int n_wg, float up) {
   using Cfg = DkdvTile<T, D, DV, QS, SW>;
   using LE = typename Planes<T>::E;  // element of an LDS tile
   constexpr int KWAVES = 4 / SW;  // 32-key columns of the workgroup
@@ -272,6 +286,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
   const int h = lane >> 5, c = lane & 31;
 
   const int wave_k = SW > 1 ? wave % KWAVES : wave, wave_q = SW > 1 ? wave / KWAVES : 0;
+  Range<T> range(up);
   const TileItem item = tile_item(w, n_wg, p.n_ktiles, CAUSAL ? p.tile_order : 0);
   const int kt_idx = item.tile;  // heaviest (earliest keys) first under causal
   const int bh = bh_of_group(item.group, p.bh, p.heads);
@@ -307,7 +322,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
   Frag<T> kf[K_LDS ? 1 : KC], vf[KCV];
 #pragma unroll
   for (int kc = 0; kc < KC; ++kc) {
-    const Frag<T> f = key < p.n_k ? ld_frag_as<T, T>(kg + key * p.sk.r + 16 * kc + 8 * h) : zero_frag<T>();
+    const Frag<T> f = key < p.n_k ? ld_frag_as<T, T>(kg + key * p.sk.r + 16 * kc + 8 * h, range) : zero_frag<T>();
     if constexpr (K_LDS) *reinterpret_cast<Frag<T>*>(kslot + 8 * Cfg::NT * kc) = f;
     else kf[kc] = f;
   }
@@ -317,7 +332,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
   };
 #pragma unroll
   for (int kc = 0; kc < KCV; ++kc)
-    vf[kc] = key < p.n_k ? ld_frag_as<T, T>(vg + key * p.sv.r + 16 * kc + 8 * h) : zero_frag<T>();
+    vf[kc] = key < p.n_k ? ld_frag_as<T, T>(vg + key * p.sv.r + 16 * kc + 8 * h, range) : zero_frag<T>();
 
   wait_global_loads();
 
@@ -384,7 +399,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
         const int cpr = is_o ? Cfg::CPRO : Cfg::CPRQ;
         const int row = rem / cpr, col = rem % cpr;
         st_chunk8<T>(base + (is_o ? Cfg::NP * Cfg::TILEQ + row * RSO : row * RSQ) + 8 * col,
-                     is_o ? Cfg::TILEO : Cfg::TILEQ, stage[i]);
+                     is_o ? Cfg::TILEO : Cfg::TILEQ, stage[i], range);
       }
     }
     if (tid < 2 * Cfg::BQ) {
@@ -392,7 +407,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
       // P = 2^(c*acc) (c = scale*log2 e), dP - D makes dS = P*acc.  Rows past
       // n_q start at -inf, so their weights are 0.
       float* f = reinterpret_cast<float*>(stage_base(buf) + Cfg::STAGE_ELEMS * Cfg::E);
-      f[tid] = stage_f;
+      f[tid] = scaled_init(stage_f, range);
     }
   };
 
@@ -463,7 +478,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
   };
 
   const int qrow = perm32(c);
-  const float cl2 = p.scale_log2;
+  const float cl2 = p.scale_log2 * range.down2;
 
   if constexpr (ASYNC) {
     if (n_iters > 0) {
@@ -632,8 +647,8 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const float pr = fast_exp2(s[qs][r] * cl2);
-            s[qs][r] = pr;                // P
-            dp[qs][r] = pr * dp[qs][r];   // dS = P (dP - D)
+            s[qs][r] = pr;                               // P
+            dp[qs][r] = pr * (dp[qs][r] * range.down2);  // dS = P (dP - D)
           }
         }
         // dV += P^T dO and dK += dS^T Q (A: lane = key row, k = queries).
@@ -645,8 +660,8 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
             tp[e] = s[qc >> 1][8 * (qc & 1) + e];
             td[e] = dp[qc >> 1][8 * (qc & 1) + e];
           }
-          const Frag<T> pa = to_frag<T>(tp);
-          const Frag<T> da = to_frag<T>(td);
+          const Frag<T> pa = to_frag<T>(tp, range.up);
+          const Frag<T> da = to_frag<T>(td, range.up);
 #pragma unroll
           for (int dt = 0; dt < NDTM; ++dt) {
             if (dt < NDTV) dv[dt] = mma(pa, col_o(qc, dt), dv[dt]);
@@ -689,6 +704,8 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
     }
   }
 
+  if (wide_range<T>(range, smem_raw)) return true;
+
   // SW > 1: add the partial sums of the SW waves that share a key column (each
   // took every SW-th 32 QS queries).  The wave with wave_q == i % SW owns
   // 32-feature tile i: the others hand it their registers, it adds them in
@@ -727,7 +744,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
     for (int r = 0; r < 16; ++r) {
       const int64_t kr = kw + c_row(r, h);
       if (kr < p.n_k)  // keys past the valid length get zero gradients
-        dkg[kr * p.sdk.r + 32 * dt + c] = kr < n_kv ? (T)(dk[dt][r] * p.scale) : (T)0.0f;
+        dkg[kr * p.sdk.r + 32 * dt + c] = kr < n_kv ? (T)(dk[dt][r] * range.down2 * p.scale) : (T)0.0f;
     }
   }
 #pragma unroll
@@ -736,9 +753,10 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int w, int n_wg) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int64_t kr = kw + c_row(r, h);
-      if (kr < p.n_k) dvg[kr * p.sdv.r + 32 * dt + c] = kr < n_kv ? (T)dv[dt][r] : (T)0.0f;
+      if (kr < p.n_k) dvg[kr * p.sdv.r + 32 * dt + c] = kr < n_kv ? (T)(dv[dt][r] * range.down2) : (T)0.0f;
     }
   }
+  return false;
 }
 
 // -------------------------------------------------- dK, dV (two groups)
@@ -1224,7 +1242,7 @@ struct DqTile {
 // share 32 QT queries and split the keys between them, BKW keys each of every
 // staged tile.
 template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, int OCC, bool CAUSAL>
-__device__ __forceinline__ void dq_tile(const BwdParams& p, int w, int n_wg, bool light_first) {
+__device__ __forceinline__ bool dq_tile(const BwdParams& p, int w, int n_wg, bool light_first, float up) {
   constexpr int NT = 256;
   constexpr int QWAVES = 4 / SW;
   constexpr int BQ = QWAVES * 32 * QT;  // queries per workgroup
@@ -1260,6 +1278,7 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, int n_wg, boo
   const int h = lane >> 5, c = lane & 31;
 
   const int wave_q = SW > 1 ? wave % QWAVES : wave, wave_k = SW > 1 ? wave / QWAVES : 0;
+  Range<T> range(up);
   const int ksub = BKW * wave_k;  // first key of this wave in a staged tile
   const TileItem item = tile_item(w, n_wg, p.n_qtiles, CAUSAL ? p.tile_order : 0);
   const int qt_idx = item.tile;
@@ -1285,14 +1304,14 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, int n_wg, boo
     const bool valid = query < p.n_q;
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
-      qf[t][kc] = valid ? ld_frag_as<T, T>(qg + query * p.sq.r + 16 * kc + 8 * h) : zero_frag<T>();
+      qf[t][kc] = valid ? ld_frag_as<T, T>(qg + query * p.sq.r + 16 * kc + 8 * h, range) : zero_frag<T>();
     }
 #pragma unroll
     for (int kc = 0; kc < KCV; ++kc) {
-      gf[t][kc] = valid ? ld_frag_as<T, TO>(dog + query * p.sdo.r + 16 * kc + 8 * h) : zero_frag<T>();
+      gf[t][kc] = valid ? ld_frag_as<T, TO>(dog + query * p.sdo.r + 16 * kc + 8 * h, range) : zero_frag<T>();
     }
-    s_init[t] = valid ? row_init(query, true) : -INFINITY;
-    dp_init[t] = valid ? row_init(query, false) : 0.0f;
+    s_init[t] = valid ? scaled_init(row_init(query, true), range) : -INFINITY;
+    dp_init[t] = valid ? scaled_init(row_init(query, false), range) : 0.0f;
   }
   wait_global_loads();
 
@@ -1342,7 +1361,7 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, int n_wg, boo
       const int rem = is_v ? chunk - BK * CPRK : chunk;
       const int cpr = is_v ? CPRV : CPRK;
       const int row = rem / cpr, col = rem % cpr;
-      st_chunk8<T>(base + (is_v ? TK + row * RSV : row * RSK) + 8 * col, is_v ? TILEV : TILEK, stage[i]);
+      st_chunk8<T>(base + (is_v ? TK + row * RSV : row * RSK) + 8 * col, is_v ? TILEV : TILEK, stage[i], range);
     }
   };
 
@@ -1377,7 +1396,7 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, int n_wg, boo
   };
 
   const int krow = perm32(c);
-  const float cl2 = p.scale_log2;
+  const float cl2 = p.scale_log2 * range.down2;
 
   if constexpr (SWZ) {
     if (n_tiles > 0) {
@@ -1476,7 +1495,7 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, int n_wg, boo
         for (int r = 0; r < 16; ++r) {
           float pr = fast_exp2(s[kt][t][r] * cl2);
           if (MASK && 32 * kt + permuted_row(r, h) >= lim) pr = 0.0f;
-          dp[kt][t][r] = pr * dp[kt][t][r];  // dS^T
+          dp[kt][t][r] = pr * (dp[kt][t][r] * range.down2);  // dS^T
         }
     }
     // dQ^T += K^T dS^T.
@@ -1488,7 +1507,7 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, int n_wg, boo
         float td[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) td[e] = dp[pc >> 1][t][8 * (pc & 1) + e];
-        b[t] = to_frag<T>(td);
+        b[t] = to_frag<T>(td, range.up);
       }
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) {
@@ -1534,6 +1553,8 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, int n_wg, boo
   for (; it < n_plain; ++it) run(BoolC<false>{}, it);
   for (; it < n_tiles; ++it) run(BoolC<true>{}, it);
 
+  if (wide_range<T>(range, smem_raw)) return true;
+
   // SW > 1: add the partial sums of the SW waves that share the queries, as in
   // dkdv_tile.
   if constexpr (SW > 1) {
@@ -1567,11 +1588,12 @@ __device__ __forceinline__ void dq_tile(const BwdParams& p, int w, int n_wg, boo
       for (int a4 = 0; a4 < 4; ++a4) {
         typename FragT<T>::half v4;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v4[e] = (T)(acc[t][dt][4 * a4 + e] * p.scale);
+        for (int e = 0; e < 4; ++e) v4[e] = (T)(acc[t][dt][4 * a4 + e] * range.down2 * p.scale);
         *reinterpret_cast<typename FragT<T>::half*>(dqg + 32 * dt + 8 * a4 + 4 * h) = v4;
       }
     }
   }
+  return false;
 }
 
 // ------------------------------------------------------- dQ (two groups)
@@ -2069,10 +2091,14 @@ void attn_bwd_kernel(BwdParams p) {
   // 69.6 -> 65.0 us, 1x8x4096 116.8 -> 109.3).  With more rounds the heaviest
   // go first.
   const bool light_first = n_kv > 0 && (int)gridDim.x <= 256 * OCC;
+  float up = range_start<T>(p.scale_log2);
   if constexpr (PARTS & 1)
-    if (b < n_kv) dkdv_tile<T, TO, D, DV, S::QS, SW, OCC, CAUSAL>(p, b, n_kv);
+    if (b < n_kv)
+      while (dkdv_tile<T, TO, D, DV, S::QS, SW, OCC, CAUSAL>(p, b, n_kv, up)) up = 1.0f;
   if constexpr (PARTS & 2)
-    if (b >= n_kv) dq_tile<T, TO, D, DV, S::QT, S::BK, SW, OCC, CAUSAL>(p, b - n_kv, (int)gridDim.x - n_kv, light_first);
+    if (b >= n_kv)
+      while (dq_tile<T, TO, D, DV, S::QT, S::BK, SW, OCC, CAUSAL>(p, b - n_kv, (int)gridDim.x - n_kv, light_first, up))
+        up = 1.0f;
 }
 
 template <typename T, typename TO, int D, int DV, int SW, int PARTS, bool CAUSAL>

@@ -32,7 +32,7 @@ template <> struct FragT<__bf16> { typedef bf16x8 type; typedef bf16x4 half; };
 template <> struct FragT<_Float16> { typedef f16x8 type; typedef f16x4 half; };
 // Eight float32 values as bf16 parts: hi + mid + lo, each the rounding of what
 // the parts before it leave (the differences are exact in float32, so the sum
-// is the value: 8 + 8 + 8 significant bits).
+// is the value: 8 + 8 + 8 significant bits; see Range for its ends).
 struct Split3 {
   bf16x8 p[3];
 };
@@ -48,34 +48,100 @@ __device__ __forceinline__ f32x16 mma(const f16x8& a, const f16x8& b, const f32x
 }
 // float32: the six products of parts down to 2^-16 of the first, smallest
 // first; the three left out are below 2^-24 of it.  Six bf16 MFMAs take 192
-// cycles where eight 32x32x2 float32 MFMAs take 512, and round less often:
-// relative error of dot products of N(0, 1) vectors against float64, float32
-// MFMAs / these, 1.5e-7 / 1.1e-7 over 64 terms, 5.9e-7 / 5.1e-7 over 1024,
-// 1.7e-6 / 1.4e-6 over 8192.
-__device__ __forceinline__ f32x16 mma(const Split3& a, const Split3& b, f32x16 c) {
+// cycles where eight 32x32x2 float32 MFMAs take 512, and round less often; the
+// forward's scores keep the five small products (mma_rest) in a sum of their
+// own, so that the first ones round once per chunk.  Errors against float64,
+// float32 MFMAs / these: o and dk of 2x4096x4096, d = 64, 5.1e-7 / 2.1e-7 and
+// 2.1e-6 / 1.8e-6; o at 4x3x2 7.2e-8 / 5.6e-8 (8.6e-8 with the scores' products
+// in one sum); a lone product of values in [1, 2), through the lse of one key,
+// 2.1 / 2.2 at most and 0.64 / 0.64 rms in units of 2^-24.
+__device__ __forceinline__ f32x16 mma_rest(const Split3& a, const Split3& b, f32x16 c) {
   c = mma(a.p[0], b.p[2], c);
   c = mma(a.p[2], b.p[0], c);
   c = mma(a.p[1], b.p[1], c);
   c = mma(a.p[0], b.p[1], c);
-  c = mma(a.p[1], b.p[0], c);
-  return mma(a.p[0], b.p[0], c);
+  return mma(a.p[1], b.p[0], c);
+}
+__device__ __forceinline__ const bf16x8& lead(const Split3& a) { return a.p[0]; }
+__device__ __forceinline__ f32x16 mma(const Split3& a, const Split3& b, const f32x16& c) {
+  return mma(lead(a), lead(b), mma_rest(a, b, c));
 }
 
-// The parts of eight float32 values.  RAW values (read from memory) may be
-// infinite or above the largest bf16: hi and mid are held to the bf16 range,
-// so that an infinity ends up in lo alone and its products keep their sign.
-template <bool RAW>
-__device__ __forceinline__ Split3 split8(const float* x) {
+// float32 operands are split times a power of two, `up`.  bf16 has no bits below
+// 2^-133, so the parts of a value below 2^-110 lose its last bits (all but 8 at
+// 2^-126); times 2^16 every float32 number, down to the smallest subnormal, is
+// the sum of its parts.  `top` is the largest magnitude a thread has split: a
+// workgroup that finds one above kRangeTop, beyond which sums of products could
+// overflow, does its tile again with up = 1 (wide_range), where hi and mid are
+// held to the bf16 range, so that an infinity ends up in lo alone and its
+// products keep their sign.  Beside values above 2^18 those below 2^-110 lose
+// bits.  Scaling and watching cost 2-8 % of the large kernels' time and 1-2 us of
+// the smallest's (2x16x4000 causal, d = 64, forward 412 / 436 us, backward 1347 /
+// 1381; float32 MFMAs 818 and 2406).
+template <typename T> struct Range {
+  static constexpr float up = 1.0f, down = 1.0f, down2 = 1.0f;
+  __device__ __forceinline__ explicit Range(float) {}
+  __device__ __forceinline__ void see(float) {}
+};
+constexpr float kRangeUp = 0x1p16f, kRangeTop = 0x1p18f;
+template <> struct Range<float> {
+  float up, down, down2;  // down = 1 / up, down2 = 1 / up^2
+  float top = 0.0f;       // times up
+  __device__ __forceinline__ explicit Range(float u) : up(u), down(1.0f / u), down2(down * down) {}
+  __device__ __forceinline__ void see(float x) { top = fmaxf(top, fabsf(x)); }
+};
+// `up` to start with (scales so small that scale / up^2 loses bits: 1).
+template <typename T>
+__device__ __forceinline__ float range_start(float scale_log2) {
+  return sizeof(T) == 2 || scale_log2 < 0x1p-90f ? 1.0f : kRangeUp;
+}
+// Whether a workgroup of 4 waves must do its tile again (uniform; flags: free
+// LDS, and free again afterwards).
+template <typename T>
+__device__ __forceinline__ bool wide_range(const Range<T>& g, unsigned char* flags) {
+  if constexpr (sizeof(T) == 2) {
+    return false;
+  } else {
+    if (g.up == 1.0f) return false;
+    uint32_t* f = reinterpret_cast<uint32_t*>(flags);
+    if ((threadIdx.x & 63) == 0) f[threadIdx.x >> 6] = 0;
+    if (g.top > kRangeTop * kRangeUp) f[threadIdx.x >> 6] = 1;
+    __syncthreads();
+    const bool r = (f[0] | f[1] | f[2] | f[3]) != 0;
+    __syncthreads();
+    return r;
+  }
+}
+
+// The parts of eight computed float32 values.
+__device__ __forceinline__ Split3 split8(const float* x, float up) {
+  Split3 s;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float y = x[e] * up;
+    const __bf16 hi = (__bf16)y;
+    const float r1 = y - (float)hi;
+    const __bf16 mid = (__bf16)r1;
+    s.p[0][e] = hi;
+    s.p[1][e] = mid;
+    s.p[2][e] = (__bf16)(r1 - (float)mid);
+  }
+  return s;
+}
+// The parts of eight float32 values read from memory, of any size.
+__device__ __forceinline__ Split3 split8(const float* x, Range<float>& g) {
   constexpr float kMax = 0x1.fep127f;  // largest finite bf16
   Split3 s;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const __bf16 hi = (__bf16)(RAW ? __builtin_amdgcn_fmed3f(x[e], -kMax, kMax) : x[e]);
-    const float r1 = x[e] - (float)hi;
-    const __bf16 mid = (__bf16)(RAW ? __builtin_amdgcn_fmed3f(r1, -kMax, kMax) : r1);
+    const float y = x[e] * g.up;
+    const __bf16 hi = (__bf16)__builtin_amdgcn_fmed3f(y, -kMax, kMax);
+    const float r1 = y - (float)hi;
+    const __bf16 mid = (__bf16)__builtin_amdgcn_fmed3f(r1, -kMax, kMax);
     s.p[0][e] = hi;
     s.p[1][e] = mid;
     s.p[2][e] = (__bf16)(r1 - (float)mid);
+    g.see(y);
   }
   return s;
 }
@@ -279,11 +345,12 @@ __device__ __forceinline__ void copy_to_lds16_sb(const void* base, unsigned voff
 }
 #pragma clang diagnostic pop
 
-// Convert eight float32 values to a fragment of T (round to nearest even).
+// Convert eight computed float32 values to a fragment of T (round to nearest
+// even; float32: their parts times up).
 template <typename T>
-__device__ __forceinline__ Frag<T> to_frag(const float* x) {
+__device__ __forceinline__ Frag<T> to_frag(const float* x, float up = 1.0f) {
   if constexpr (sizeof(T) == 4) {
-    return split8<false>(x);
+    return split8(x, up);
   } else {
     Frag<T> r;
 #pragma unroll
@@ -379,14 +446,14 @@ __device__ __forceinline__ Chunk8<T> ld_chunk8(const TO* src) {
   }
 }
 template <typename T>
-__device__ __forceinline__ void st_chunk8(typename Planes<T>::E* dst, int plane, const Chunk8<T>& c) {
+__device__ __forceinline__ void st_chunk8(typename Planes<T>::E* dst, int plane, const Chunk8<T>& c, Range<T>& g) {
   if constexpr (sizeof(T) == 2) {
     st16(dst, c);
   } else {
     float x[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[e] = c[e];
-    const Split3 s = split8<true>(x);
+    const Split3 s = split8(x, g);
 #pragma unroll
     for (int i = 0; i < 3; ++i) st16(dst + i * plane, __builtin_bit_cast(u32x4, s.p[i]));
   }
@@ -394,7 +461,7 @@ __device__ __forceinline__ void st_chunk8(typename Planes<T>::E* dst, int plane,
 
 // Eight consecutive elements of a TO array as a fragment of T.
 template <typename T, typename TO>
-__device__ __forceinline__ Frag<T> ld_frag_as(const TO* src) {
+__device__ __forceinline__ Frag<T> ld_frag_as(const TO* src, Range<T>& g) {
   if constexpr (sizeof(T) == 2 && __is_same(T, TO)) {
     return *reinterpret_cast<const Frag<T>*>(src);
   } else {
@@ -406,7 +473,7 @@ __device__ __forceinline__ Frag<T> ld_frag_as(const TO* src) {
       x[e] = a[e];
       x[4 + e] = b[e];
     }
-    if constexpr (sizeof(T) == 4) return split8<true>(x);
+    if constexpr (sizeof(T) == 4) return split8(x, g);
     else return to_frag<T>(x);
   }
 }

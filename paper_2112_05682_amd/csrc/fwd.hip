@@ -75,8 +75,10 @@ struct FwdTile {
 #ifndef MEA_FWD_ILV
 #define MEA_FWD_ILV 1
 #endif
+// One workgroup's tile of queries and key range.  Returns whether it is to be
+// done again with up = 1 (float32; nothing is written then).
 template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, int OCC, bool CAUSAL>
-__global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
+__device__ __forceinline__ bool fwd_tile(const FwdParams& p, float up) {
   using Cfg = FwdTile<T, D, DV, QT, BKW, SW, OCC>;
   constexpr int BK = Cfg::BK, QWAVES = 4 / SW;
   using LE = typename Planes<T>::E;  // element of an LDS tile
@@ -93,6 +95,7 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
   const int h = lane >> 5, c = lane & 31;
+  Range<T> range(up);
 
   // ---- workgroup -> (split, bh, query tile); heaviest causal tiles first.
   const TileItem item = tile_item(blockIdx.x, gridDim.x, p.n_qtiles, CAUSAL ? p.tile_order : 0);
@@ -124,7 +127,7 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
     const int64_t row = qw + 32 * t + c;
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc)
-      qf[t][kc] = row < p.n_q ? ld_frag_as<T, T>(qg + row * p.sq.r + 16 * kc + 8 * h) : zero_frag<T>();
+      qf[t][kc] = row < p.n_q ? ld_frag_as<T, T>(qg + row * p.sq.r + 16 * kc + 8 * h, range) : zero_frag<T>();
   }
 
   wait_global_loads();
@@ -170,7 +173,7 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
     const int cpr = is_v ? Cfg::CPRV : Cfg::CPRK;
     const int row = rem / cpr, col = rem % cpr;
     st_chunk8<T>(smem + buf * Cfg::STAGE + (is_v ? Cfg::NP * Cfg::TILEK + row * RSV : row * RSK) + 8 * col,
-                 is_v ? Cfg::TILEV : Cfg::TILEK, x);
+                 is_v ? Cfg::TILEV : Cfg::TILEK, x, range);
   };
   auto load_stage = [&](int64_t k0) __attribute__((always_inline)) {
     if constexpr (EARLY)
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
   };
 
   const int krow = perm32(c);  // key row this lane feeds into the A operand
-  const float cl2 = p.scale_log2;
+  const float cl2 = p.scale_log2 * range.down2;
 
   // Number of leading tiles that need no mask: every key exists (no ragged
   // tail) and, under the causal mask, precedes the workgroup's first query.
@@ -217,14 +220,30 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
       for (int t = 0; t < QT; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[kt][t][r] = 0.0f;
+    // float32: the small products have a sum of their own, added once.
+    constexpr bool F32 = sizeof(T) == 4;
+    f32x16 rest[F32 ? NKT : 1][F32 ? QT : 1] = {};
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
 #pragma unroll
       for (int kt = 0; kt < NKT; ++kt) {
         const Frag<T> a = lds_frag_planes<T>(ks + (32 * kt + krow) * RSK + 16 * kc + 8 * h, Cfg::TILEK);
 #pragma unroll
-        for (int t = 0; t < QT; ++t) s[kt][t] = mma(a, qf[t][kc], s[kt][t]);
+        for (int t = 0; t < QT; ++t) {
+          if constexpr (F32) {
+            rest[kt][t] = mma_rest(a, qf[t][kc], rest[kt][t]);
+            s[kt][t] = mma(lead(a), lead(qf[t][kc]), s[kt][t]);
+          } else {
+            s[kt][t] = mma(a, qf[t][kc], s[kt][t]);
+          }
+        }
       }
+    }
+    if constexpr (F32) {
+#pragma unroll
+      for (int kt = 0; kt < NKT; ++kt)
+#pragma unroll
+        for (int t = 0; t < QT; ++t) s[kt][t] += rest[kt][t];
     }
 
     if constexpr (MASK) {
@@ -280,7 +299,7 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
         float e8[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) e8[e] = fast_exp2(fmaf(s[pc >> 1][t][8 * (pc & 1) + e], cl2, neg[t]));
-        pf[t][pc] = to_frag<T>(e8);
+        pf[t][pc] = to_frag<T>(e8, range.up);
         l_run[t] = tree_sum<8>(e8, l_run[t]);
       }
     }
@@ -327,8 +346,8 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
     }
     // O^T += V^T P^T; each V^T fragment feeds every query sub-tile.
     // float32: a tile's products are summed apart and added to the numerator
-    // once, so that it rounds once per tile and not 6 NPC times (relative error
-    // of o over 60000 keys 1.2e-6 without this; 1.1e-6 with float32 MFMAs).
+    // once (relative error of o over 60000 keys 3.9e-7; 6.3e-7 with float32 MFMAs
+    // into the numerator).
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt) {
       if constexpr (sizeof(T) == 4) {
@@ -336,11 +355,9 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
         for (int t = 0; t < QT; ++t) {
           f32x16 sum = {};
 #pragma unroll
-          for (int pc = 0; pc < NPC; ++pc) {
-            const Frag<T> a = col_v(pc, dt);
-            sum = mma(a, pf[t][pc], sum);
-          }
-          acc[t][dt] += sum;
+          for (int pc = 0; pc < NPC; ++pc) sum = mma(col_v(pc, dt), pf[t][pc], sum);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[t][dt][r] = fmaf(sum[r], range.down2, acc[t][dt][r]);
         }
       } else {
 #pragma unroll
@@ -374,6 +391,7 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
   int it = 0;
   for (; it < n_plain; ++it) step(BoolC<false>{}, it);
   for (; it < n_tiles; ++it) step(BoolC<true>{}, it);
+  if (wide_range<T>(range, smem_raw)) return true;
 
   // ---- SW > 1: one summary of the waves that share the queries (Section 4's
   // combine): rescale to the common maximum and add, in the order of the
@@ -475,6 +493,13 @@ __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
       }
     }
   }
+  return false;
+}
+
+template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, int OCC, bool CAUSAL>
+__global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
+  float up = range_start<T>(p.scale_log2);
+  while (fwd_tile<T, TO, D, DV, QT, BKW, SW, OCC, CAUSAL>(p, up)) up = 1.0f;
 }
 
 // ---------------------------------------------------------------------------
