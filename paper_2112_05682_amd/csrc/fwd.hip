@@ -420,7 +420,8 @@ __device__ __forceinline__ bool fwd_tile(const FwdParams& p, float up) {
       for (int y = 0; y < SW; ++y) {
         const int i = ((wave_q + y * QWAVES) * QT + t) * 32 + c;
         const float m_y = red_m[i];
-        l_g += m_y == -INFINITY ? 0.0f : fast_exp2(m_y - m_g) * red_l[i];
+        // (0 times a NaN denominator, a share of NaN scores only, stays NaN)
+        l_g += (m_y == -INFINITY ? 0.0f : fast_exp2(m_y - m_g)) * red_l[i];
       }
       const float f = m_ref[t] == -INFINITY ? 0.0f : fast_exp2(m_ref[t] - m_g);
       m_ref[t] = m_g;

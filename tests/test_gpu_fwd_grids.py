@@ -97,6 +97,21 @@ def test_rows_without_keys(d):
     assert (o[0] == 0).all() and (lse[0] == -float("inf")).all() and torch.isfinite(lse[1]).all()
 
 
+@gpu
+@pytest.mark.parametrize("dtype,d,first", [("bf16", 64, 32), ("bf16", 64, 96), ("bf16", 128, 32), ("fp32", 64, 32),
+                                           ("fp32", 128, 32)])
+def test_nan_scores_of_one_wave(dtype, d, first):
+    # Keys that one of the waves sharing a tile's queries has for itself, all NaN:
+    # o is NaN and lse -inf, as where one wave sees them beside other keys.
+    n = first + 7
+    g = to_gpu(attention_inputs(1, 1, 70, n, d, dtype, with_grad=False))
+    for i in (first, 3):
+        k = g["k"].clone()
+        k[0, 0, i:n if i == first else i + 1] = float("nan")
+        o, lse = attention_fwd(g["q"], k, g["v"])
+        assert o.isnan().all() and (lse == -float("inf")).all()
+
+
 def test_tile_orders_cover_every_item_once():
     """The three orders of causal_tile_order (tile_item in device.hpp), restated:
     each maps the workgroups of a grid to its (tile, group) items one to one."""
