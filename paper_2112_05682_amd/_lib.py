@@ -106,6 +106,9 @@ def load(path: str = LIB_PATH):
 
 
 _native = None
+# The entry points that the extension calls, in the order of its init.
+NATIVE_CALLS = ("mea_attention_fwd_workspace_size", "mea_attention_bwd_workspace_size", "mea_attention_fwd",
+                "mea_attention_bwd")
 
 
 def native():
@@ -119,9 +122,7 @@ def native():
         loader = importlib.machinery.ExtensionFileLoader(__package__ + "._torch_ext", EXT_PATH)
         ext = importlib.util.module_from_spec(importlib.util.spec_from_loader(loader.name, loader))
         loader.exec_module(ext)
-        ext.init(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
-                   for name in ("mea_attention_fwd_workspace_size", "mea_attention_bwd_workspace_size",
-                                "mea_attention_fwd", "mea_attention_bwd")))
+        ext.init(check, *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in NATIVE_CALLS))
         _native = ext
     return _native
 

@@ -1,15 +1,17 @@
 // Native argument marshalling between torch tensors and the C ABI (mea.h): the
 // ordinary case of attention.py's calls -- plain GPU tensors whose layout the
 // kernels read in place -- as one call each.  Every function returns None for
-// anything else, before it allocates or launches; attention.py then takes its
-// general path, which copies or raises.
+// anything else, and for what the library refuses, before anything is launched;
+// attention.py then takes its general path, which copies or raises.  A launch
+// that fails is raised here, and not tried again.
 //
 // Why it exists: a training step on a small problem is bound by the host.
 // Autograd runs the backward on a thread of its own, and each hand-over leaves
 // the interpreter's working set cold, so the marshalling in Python, 52 us in a
 // loop on one thread, took 178 us of every 1x1x256x256 forward + backward.
 // The functions are found by address (init), so this module links to torch
-// only and uses the library that _lib.load() loaded.
+// only and uses the library that _lib.load() loaded; errors are raised by
+// _lib.check.
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -28,6 +30,7 @@ decltype(&mea_attention_fwd_workspace_size) g_fwd_ws;
 decltype(&mea_attention_bwd_workspace_size) g_bwd_ws;
 decltype(&mea_attention_fwd) g_fwd;
 decltype(&mea_attention_bwd) g_bwd;
+PyObject* g_check;  // check(name, status): raises what a status means
 
 // A plain torch.Tensor or Parameter with storage on a GPU (no subclass, no
 // functorch wrapper), or null.
@@ -103,6 +106,13 @@ at::Tensor workspace(size_t bytes, const at::Device& dev) {
 }
 
 PyObject* none() { Py_RETURN_NONE; }
+
+// The result of a call whose status is not MEA_OK: None where the library
+// refused the arguments (it launches nothing then), else the error.
+PyObject* failed(const char* name, mea_status st) {
+  if (st == MEA_ERR_INVALID_ARG || st == MEA_ERR_UNSUPPORTED) return none();
+  return PyObject_CallFunction(g_check, "si", name, (int)st);
+}
 
 // A new tuple of tensors; undefined ones are None.
 PyObject* tuple_of(std::initializer_list<at::Tensor> ts) {
@@ -180,7 +190,7 @@ PyObject* ext_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
                     residual && out_dt != at::kFloat ? &o_lo : nullptr, at::IntArrayRef(shape, 3),
                     at::IntArrayRef(shape, 4), out_dt);
   }
-  if (st != MEA_OK) return none();
+  if (st != MEA_OK) return failed("mea_attention_fwd", st);
   return residual ? tuple_of({o, lse, o_lo}) : tuple_of({o, lse});
   END_HANDLE_TH_ERRORS
 }
@@ -271,7 +281,7 @@ PyObject* ext_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
                     o_lo ? o_lo->const_data_ptr() : nullptr, d_o->const_data_ptr(), *lse, ptr(g[0]), ptr(g[1]),
                     ptr(g[2]));
   }
-  if (st != MEA_OK) return none();
+  if (st != MEA_OK) return failed("mea_attention_bwd", st);
   return tuple_of({g[0], g[1], g[2]});
   END_HANDLE_TH_ERRORS
 }
@@ -311,7 +321,7 @@ PyObject* ext_packed_fwd(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     st = launch_fwd(p, *t, packed_part(*t, 1), packed_part(*t, 2), o.mutable_data_ptr(), &lse,
                     dt != at::kFloat ? &o_lo : nullptr, {B, H, n}, {B, H, n, d}, dt);
   }
-  if (st != MEA_OK) return none();
+  if (st != MEA_OK) return failed("mea_attention_fwd", st);
   return tuple_of({o, lse, o_lo});
   END_HANDLE_TH_ERRORS
 }
@@ -353,23 +363,26 @@ PyObject* ext_packed_bwd(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
                     o_lo ? o_lo->const_data_ptr() : nullptr, d_o->const_data_ptr(), *lse, packed_part(g, 0),
                     packed_part(g, 1), packed_part(g, 2));
   }
-  if (st != MEA_OK) return none();
+  if (st != MEA_OK) return failed("mea_attention_bwd", st);
   return THPVariable_Wrap(g);
   END_HANDLE_TH_ERRORS
 }
 
-// init(fwd_workspace_size, bwd_workspace_size, fwd, bwd): the addresses of the
-// library's entry points.
+// init(check, fwd_workspace_size, bwd_workspace_size, fwd, bwd): _lib.check and
+// the addresses of the library's entry points.
 PyObject* ext_init(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  if (n != 4) {
-    PyErr_SetString(PyExc_TypeError, "init takes four addresses");
+  if (n != 5) {
+    PyErr_SetString(PyExc_TypeError, "init takes a function and four addresses");
     return nullptr;
   }
   void* f[4];
   for (int i = 0; i < 4; ++i) {
-    f[i] = PyLong_AsVoidPtr(a[i]);
+    f[i] = PyLong_AsVoidPtr(a[i + 1]);
     if (PyErr_Occurred()) return nullptr;
   }
+  PyObject* old = g_check;
+  g_check = Py_NewRef(a[0]);
+  Py_XDECREF(old);
   g_fwd_ws = reinterpret_cast<decltype(g_fwd_ws)>(f[0]);
   g_bwd_ws = reinterpret_cast<decltype(g_bwd_ws)>(f[1]);
   g_fwd = reinterpret_cast<decltype(g_fwd)>(f[2]);

@@ -2,6 +2,8 @@
 (the same library underneath): the same bits for every layout, option and
 output form that the native calls accept, and None for what they leave to the
 general path."""
+import ctypes
+
 import pytest
 import torch
 
@@ -116,3 +118,40 @@ def test_native_calls_leave_other_inputs_to_the_general_path():
     assert n.bwd(q, k, v, o, lse, do, False, None, False, False, None, None, o_lo) is None
     assert n.bwd(q, k, v, o, lse, do.float(), False, None, True, True, None, None, o_lo) is None
     assert n.bwd(q, k, v, o, lse[:, :, :5], do, False, None, True, True, None, None, o_lo) is None
+
+
+@pytest.mark.parametrize("status,raised", [(_lib.MEA_ERR_HIP, True), (_lib.MEA_ERR_WORKSPACE, True),
+                                           (_lib.MEA_ERR_INVALID_ARG, False), (_lib.MEA_ERR_UNSUPPORTED, False)])
+def test_failed_launches_are_raised_and_not_repeated(status, raised):
+    """A library whose launches fail (stand-ins on the host): the native calls raise
+    the status, and return None for what the library refuses before a launch."""
+    n, lib, calls = _lib.native(), _lib.load(), []
+    real = [ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _lib.NATIVE_CALLS]
+    stand_in = ctypes.CFUNCTYPE(ctypes.c_int)(lambda: calls.append(1) or status)
+    fake = ctypes.cast(stand_in, ctypes.c_void_p).value
+    q, k, v, do = tensors("contiguous", torch.bfloat16, 64, 64)
+    qkv, dqkv = (randn(2, 50, w, 3, 64, dtype=torch.bfloat16, seed=4) for w in (3, 1))
+    o, lse, o_lo = attention_fwd(q, k, v, residual=True)
+    po, plse, po_lo = n.packed_fwd(qkv, False, None, None)
+    every = [lambda: n.fwd(q, k, v, False, None, True, None, None, None, True),
+             lambda: n.bwd(q, k, v, o, lse, do, False, None, True, True, None, None, o_lo),
+             lambda: n.packed_fwd(qkv, False, None, None),
+             lambda: n.packed_bwd(qkv, po, plse, po_lo, dqkv[:, :, 0], False, None, None)]
+    n.init(_lib.check, *real[:2], fake, fake)
+    try:
+        for f in every:
+            if raised:
+                with pytest.raises(_lib.MeaError) as e:
+                    f()
+                assert e.value.status == status
+            else:
+                assert f() is None
+        if raised:  # through the public calls: once, and no second attempt
+            with pytest.raises(_lib.MeaError):
+                attention_fwd(q, k, v)
+            with pytest.raises(_lib.MeaError):
+                attention_bwd(q, k, v, o, lse, do)
+        assert len(calls) == (6 if raised else 4)
+    finally:
+        n.init(_lib.check, *real)
+    assert torch.equal(attention_fwd(q, k, v)[0], o)
