@@ -306,82 +306,122 @@ template <> struct FwdShape<float, 128> { static constexpr int QT = 1, BK = 32, 
 // How a forward that is not decode-shaped fills the chip: the two-group kernel
 // (waves 0; where fwd64_bq or fwd128_bq name it) or the 4-wave kernel with 1, 2
 // or 4 waves per 32 queries, and the key ranges that are combined afterwards.
-//
-// tiles = 128-query tiles of the 4-wave kernel, wgs = the two-group kernel's
-// workgroups (one per CU, so 256 a round).  More waves per 32 queries and more
-// key ranges both make more workgroups of the same work; waves re-read K and V
-// through L2 once more each, ranges cost partial sums in memory and a combine
-// launch (about 5 us), so waves fill the chip at short keys and ranges at long
-// ones.  Measured in us, forward (with its combine), bf16 unless noted,
-// before / with this rule's choice:
-//   two-group kernel, ranges of one round and not 1024 workgroups:
-//     2x16x4096 d = 64 (wgs 256) 4 ranges 213 / 1 range 160, 1x16x4096 d = 128
-//     (256) 172 / 122, 2x16x2048 d = 128 92 / 67, 1x12x4096 d = 64 (96) 87 / 73,
-//     1x1x16384 d = 64 (32) 97 / 82, 1x2x16384 d = 128 (128) 300 / 245
-//   unmasked d = 64: 1x8x1024 (tiles 64) two-group 35 / 4 waves 13, 4x8x1024
-//     (256) 35 / 2 waves 21, 1x1x4096 (32) 40 / 2 waves, 8 ranges 22, 1x4x4096
-//     (128) 47 / 1 wave, 4 ranges 39, 2x16x2048 (512) 55 / 1 wave 50, 16x12x512
-//     (768) 27 / 1 wave 25, 16x16x600 (1280; a 512-query tile is 41 % padding)
-//     58 / 1 wave 45; but 8x16x1024 (1024) 45 / 1 wave 52, 1x24x4096 (768) 117 /
-//     1 wave 134: two-group
-//   causal d = 64: 2x8x1024 (128) 20 / 4 waves 13, 4x8x1024 (256) 20 / 2 waves
-//     16, 1x8x4096 (256) 56 / 2 waves 47; d = 128: 1x32x2047 (512) two-group 91 /
-//     1 wave 62, 1x8x4000 (256) 90 / 2 waves 73, 4x8x1024 (256) 33 / 2 waves 26,
-//     16x16x600 (1280) 68 / 1 wave 63, but 4x32x2047 (2048) 179 / 1 wave 191
-//   d = 128: 1x8x2000 (128) 41 / two-group, 4 ranges 36, 1x1x2000 (16) 32 / 2
-//     waves, 8 ranges 19, 2x8x512 (64) 20 / 2 waves 15
-//   float32: 1x1x256 d = 64 18.5 / 2 waves, 4 ranges 11, 1x8x1000 (64) 37 / 4
-//     ranges 27, 1x1x2000 d = 128 (16) 83 / 2 waves, 8 ranges 37.
 struct FwdGrid {
   int waves;       // 0: two-group kernel
   int64_t ranges;  // key ranges wanted (the plan rounds them to whole tiles)
 };
 inline int64_t clamp64(int64_t x, int64_t lo, int64_t hi) { return x < lo ? lo : (x > hi ? hi : x); }
+// Keys of a staged tile of the 4-wave forward with sw waves per 32 queries.
+inline int fwd_stream_tile(bool is16, int sw) { return sw == 1 ? (is16 ? 64 : 32) : 32 * sw; }
+// What a forward kernel takes: us to start and end, and us per 1000 keys of a
+// workgroup with 1, 2 or 3 of its kind on the CU (0: that many do not fit).
+// Fitted to 19 kinds of unmasked forward, 100 to 5000 measurements each over
+// 1-200 heads, 1-16384 queries and 1-300000 keys (median errors 3-8 %).
+struct FwdRate {
+  double fixed, keys[3];
+};
+inline FwdRate fwd_rate(bool is16, int d, int dv, int waves) {
+  if (!is16) {
+    if (d == 64 && dv == 64) return waves == 1 ? FwdRate{5.3, {58.6, 92.9, 0}} : FwdRate{6.5, {43.6, 62.7, 0}};
+    if (d == dv) return waves == 1 ? FwdRate{6.6, {113, 0, 0}} : FwdRate{4.6, {99.6, 0, 0}};
+    if (d == 64) return waves == 1 ? FwdRate{6.8, {112, 151, 0}} : FwdRate{4.7, {71.3, 0, 0}};
+    return waves == 1 ? FwdRate{6.6, {102, 148, 0}} : FwdRate{4.5, {76.1, 0, 0}};
+  }
+  if (d == 64 && dv == 64) {
+    if (waves == 0) return {6.9, {27.2, 0, 0}};
+    if (waves == 1) return {4.7, {14.4, 21.5, 28.9}};
+    return waves == 2 ? FwdRate{4.8, {10.4, 14.2, 18.3}} : FwdRate{4.8, {7.05, 9.41, 0}};
+  }
+  if (d == dv) {
+    if (waves == 0) return {5.7, {23.9, 0, 0}};
+    return waves == 1 ? FwdRate{6.0, {25.2, 35.6, 0}} : FwdRate{6.4, {16.1, 23.9, 0}};
+  }
+  if (d == 64) return waves == 1 ? FwdRate{5.6, {20.7, 28.6, 0}} : FwdRate{5.7, {13.4, 19.2, 0}};
+  return waves == 1 ? FwdRate{5.0, {18.2, 27.4, 0}} : FwdRate{5.4, {12.8, 18.2, 0}};
+}
+// Unmasked forwards: the kernel and the number of ranges whose rounds take least.
+// n workgroups of L keys on 256 CUs take whole rounds of as many as fit, and a
+// last one of fewer; ranges add a combine (4 us, 6.5 more where it is staged) and
+// the writing and reading of the partial sums.  Only numbers of ranges that fill
+// another CU's worth (n just below a multiple of 256) can be the best.  Counting
+// rounds finds what thresholds on the same numbers missed, us, thresholds /
+// rounds: d = 64 1x17x8192 459 / 382, 65x1024 on 65536 keys 1988 / 1235, 136x1024
+// on 65536 2567 / 2436; d = 128 40x2000 on 16383 776 / 626, 9x4000 on 262144 5119 /
+// 3988; d = 64, d_v = 128 17x4096 on 16384 760 / 568, d = 128, d_v = 64 17x2048 on
+// 16384 420 / 285; float32 d = 64 24x1500 on 8192 679 / 478, d = 128 17x2048 on
+// 4096 884 / 610.  With at most 3 rounds of ranges in place of 9: 136x1024 on 65536
+// keys d = 64 2940.
+inline FwdGrid fwd_grid_unmasked(bool is16, int d, int dv, int64_t n_q, int64_t n_k, int64_t bh) {
+  const bool same = d == dv;
+  const int64_t bq = d == 64 ? 512 : 256;
+  FwdGrid best = {1, 1};
+  double t_best = 0;
+  for (int waves = 0; waves <= (is16 && same && d == 64 ? 4 : 2); waves += waves == 2 ? 2 : 1) {
+    // Short streams of the two-group kernel's tiles do not pay for its prologue.
+    if (waves == 0 && !(is16 && same && n_k >= 512 && (d == 64 ? fwd64_bq(n_q, bh, false) : fwd128_bq(n_q, false)) == bq))
+      continue;
+    const int64_t rows = waves ? 128 / waves : bq, q_wgs = bh * ((n_q + rows - 1) / rows);
+    const int64_t bk = waves ? fwd_stream_tile(is16, waves) : 64, k_tiles = (n_k + bk - 1) / bk;
+    const int64_t r_max = clamp64(n_k / 128, 1, 64);
+    const FwdRate k = fwd_rate(is16, d, dv, waves);
+    const int per_cu = k.keys[2] > 0 ? 3 : (k.keys[1] > 0 ? 2 : 1);
+    int64_t r_last = 0;
+    for (int64_t m = 0; m <= 9; ++m) {
+      const int64_t r = m == 0 ? 1 : clamp64(256 * m / q_wgs, 1, r_max);
+      if (r == r_last) continue;
+      r_last = r;
+      const int64_t tiles = (k_tiles + r - 1) / r, ranges = (k_tiles + tiles - 1) / tiles;
+      const int64_t on_cu = (q_wgs * ranges + 255) / 256, last = on_cu % per_cu;
+      double t = k.fixed + (double)(tiles * bk) * 1e-3 *
+                               ((double)(on_cu / per_cu) * k.keys[per_cu - 1] + (last ? k.keys[last - 1] : 0));
+      if (ranges > 1) t += 4 + (double)(bh * n_q * ranges * (dv + 2) * 8) * 0.22e-6;
+      if (ranges > kCombineGroup) t += 6.5;
+      if (t_best == 0 || t < t_best) {
+        t_best = t;
+        best = {waves, r};
+      }
+    }
+  }
+  return best;
+}
+// Causal forwards.  tiles = 128-query tiles of the 4-wave kernel, wgs = the
+// two-group kernel's workgroups.  More waves per 32 queries and more key ranges
+// both make more workgroups of the same work; waves re-read K and V through L2
+// once more each, ranges cost partial sums and a combine, so waves fill the chip
+// at short keys.  At long ones (from 3072 queries) the heaviest tile alone takes
+// twice the mean of a grid that is resident at once, and ranges of about a round
+// cut it.  us, without / with this rule's choice:
+//   d = 64: 2x8x1024 (tiles 128) two-group 20 / 4 waves 13, 4x8x1024 (256) 20 / 2
+//     waves 16; ranges 1x1x8192 (64) 66 / 33, 1x5x8192 (320) 122 / 92, 1x8x7000
+//     (440) 105 / 102, but 1x10x6000 (470) 92.7 / 95.5
+//   d = 128: 1x32x2047 (512) two-group 91 / 1 wave 62, 4x8x1024 (256) 33 / 2
+//     waves 26, 16x16x600 (1280) 68 / 1 wave 63, but 4x32x2047 (2048) 179 / 1
+//     wave 191; ranges 1x1x16384 (128) 266 / 112, 1x5x8192 (320) 206 / 110
+//   d_v != d: ranges, d = 64 1x1x16384 (128) 225 / 116, 1x5x8192 (320) 175 / 132;
+//     d = 128 1x2x8192 (128) 107 / 57
 inline FwdGrid fwd_grid(bool is16, bool causal, int d, int dv, int64_t n_q, int64_t n_k, int64_t bh) {
-  const int64_t tiles = bh * ((n_q + 127) / 128);
+  if (!causal) return fwd_grid_unmasked(is16, d, dv, n_q, n_k, bh);
+  const int64_t tiles = bh * ((n_q + 127) / 128), wgs = bh * ((n_q + 255) / 256);
   const bool same = d == dv, wide = d == 128 || dv == 128;
-  const int64_t bq = d == 64 ? 512 : 256, rows = (n_q + bq - 1) / bq * bq, wgs = bh * (rows / bq);
-  const bool two_group = is16 && same && (d == 64 ? fwd64_bq(n_q, bh, causal) : fwd128_bq(n_q, causal)) == bq;
-  const int64_t cap = n_k >= 16384 ? 64 : 8;  // at most 8 ranges but for long keys
   if (!is16) {
     const int w = tiles <= 32 ? 2 : 1;
     const int64_t slots = same && wide ? 256 : 512;
-    return {w, causal && n_k > n_q ? 1 : clamp64(slots / (tiles * w), 1, clamp64(n_k / (w == 2 ? 128 : 256), 1, cap))};
+    return {w, n_k > n_q ? 1 : clamp64(slots / (tiles * w), 1, clamp64(n_k / (w == 2 ? 128 : 256), 1, n_k >= 16384 ? 64 : 8))};
   }
-  if (causal) {
-    if (same && d == 64) {
-      if (two_group) return {0, 1};
-      return {tiles <= 128 ? 4 : (tiles <= 256 ? 2 : 1), tiles <= 32 ? clamp64(n_k / 256, 1, 4) : 1};
-    }
-    if (same && tiles > 512 && n_q > 1024) return {0, 1};
-    return {tiles <= 256 ? 2 : 1, tiles <= 64 && n_k <= n_q && n_k >= 1024 ? 2 : 1};
-  }
-  // Unmasked.  A last two-group tile that is mostly padding leaves it out.
-  const bool pp = two_group && 4 * n_q >= 3 * rows;
-  if (pp && n_k >= 512 && wgs >= 224) return {0, wgs > 256 && wgs < 512 && n_k >= 16384 ? 4 : 1};
-  const int64_t pp_ranges = clamp64(256 / wgs, 1, clamp64(n_k / 512, 1, 64));
+  const bool long_keys = n_q >= 3072 && n_k >= 3072 && n_k <= n_q;
   if (same && d == 64) {
-    if (tiles >= 512) return {pp && wgs >= 160 && n_k >= 2048 ? 0 : 1, 1};
-    if (tiles >= 256 && n_k < 4096) return {tiles <= 256 ? 2 : 1, 1};
-    if (pp && n_k >= (tiles >= 256 ? 4096 : 8192)) return {0, pp_ranges};
-    if (tiles >= 128)
-      return n_k < 2048 ? FwdGrid{2, 1} : FwdGrid{1, clamp64((n_k >= 16384 ? 768 : 512) / tiles, 1, cap)};
-    if (n_k < 2048) return {4, tiles <= 16 ? clamp64(n_k / 256, 1, 4) : 1};
-    return {2, clamp64(512 / (2 * tiles), 1, clamp64(n_k / 512, 1, cap))};
+    if (fwd64_bq(n_q, bh, true) == 512) return {0, 1};
+    if (long_keys && tiles > 32 && tiles <= 448) return {1, (767 + tiles) / tiles};
+    return {tiles <= 128 ? 4 : (tiles <= 256 ? 2 : 1), tiles <= 32 ? clamp64(n_k / 256, 1, 4) : 1};
   }
   if (same) {
-    if (pp && n_k >= (tiles >= 128 ? 1024 : 4096)) return {0, pp_ranges};
-    if (tiles >= 384) return {1, 1};
-    const int w = tiles <= 256 && n_k < 4096 ? 2 : 1;
-    return {w, n_k < 1024 && tiles > 16 ? 1 : clamp64(512 / (tiles * w), 1, clamp64(n_k / 256, 1, cap))};
+    if (tiles > 512 && n_q > 1024) return {0, 1};
+    if (long_keys && wgs < 256) return {0, clamp64((255 + wgs) / wgs, 1, 16)};
+  } else if (long_keys && tiles <= 320) {
+    return {1, clamp64((575 + tiles) / tiles, 1, 16)};
   }
-  if (tiles > 256) return {1, 1};
-  if (tiles <= 32) return {2, clamp64(512 / (2 * tiles), 1, clamp64(n_k / 512, 1, cap))};
-  if (n_k < 2048 || tiles > 128) return {n_k < 4096 ? 2 : 1, 1};
-  return {1, clamp64(512 / tiles, 1, cap)};
+  return {tiles <= 256 ? 2 : 1, tiles <= 64 && n_k <= n_q && n_k >= 1024 ? 2 : 1};
 }
-// Keys of a staged tile of the 4-wave forward with sw waves per 32 queries.
-inline int fwd_stream_tile(bool is16, int sw) { return sw == 1 ? (is16 ? 64 : 32) : 32 * sw; }
 
 // Order of a causal grid's tiles (tile_item in device.hpp).  Tile major starts
 // the heaviest tiles of every head first, so the last workgroups are light

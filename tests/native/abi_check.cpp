@@ -100,6 +100,58 @@ static void check_fwd_plan(int64_t B, int64_t H, int64_t nq, int64_t nk, int64_t
   }
 }
 
+// The grid that reaches the launcher is fwd_grid's: its kernel, ranges of whole
+// staged tiles of that kernel that cover the keys without an empty one, and
+// partials of all of them inside the workspace, for every head dimension pair.
+static void check_fwd_grid(int64_t BH, int64_t nq, int64_t nk, int64_t d, int64_t dv, int dtype, int causal) {
+  mea_problem p = prob(1, BH, nq, nk, d, dtype, causal, dv == d ? 0 : dv);
+  size_t need = 0;
+  CHECK(mea_attention_fwd_workspace_size(&p, &need) == MEA_OK, "fwd ws size");
+  CHECK(mea_attention_fwd(&p, P, P, P, P, static_cast<float*>(P), nullptr, need ? WS : nullptr, need, nullptr) == MEA_OK,
+        "fwd call %lld x %lld x %lld", (long long)BH, (long long)nq, (long long)nk);
+  const mea::FwdParams& f = mea::g_last_fwd;
+  const bool is16 = dtype != MEA_F32;
+  const mea::FwdGrid g = mea::fwd_grid(is16, causal != 0, (int)d, (int)dv, nq, nk, BH);
+  CHECK(f.stream_waves == g.waves && (g.waves == 0 || g.waves == 1 || g.waves == 2 || g.waves == 4), "kernel %d",
+        f.stream_waves);
+  CHECK(g.waves != 4 || (is16 && d == 64 && dv == 64), "four waves where no such kernel is built");
+  const int64_t bq = d == 64 ? 512 : 256;
+  CHECK(g.waves || (is16 && d == dv && f.n_qtiles == (nq + bq - 1) / bq), "two-group kernel on %lld-query tiles",
+        (long long)bq);
+  const int64_t tile = g.waves ? mea::fwd_stream_tile(is16, g.waves) : 64;
+  CHECK(g.ranges >= 1 && g.ranges <= 64 && f.n_splits <= g.ranges, "ranges %d of %lld", f.n_splits, (long long)g.ranges);
+  CHECK(f.keys_per_split % tile == 0 && f.keys_per_split * f.n_splits >= nk && f.keys_per_split * (f.n_splits - 1) < nk,
+        "ranges of whole tiles (%lld x %lld x %lld, d %lld)", (long long)BH, (long long)nq, (long long)nk, (long long)d);
+  CHECK((need == 0) == (f.n_splits == 1), "workspace iff ranges");
+  if (f.n_splits == 1) return;
+  const size_t rows = (size_t)f.n_splits * (size_t)BH * (size_t)nq;
+  CHECK(inside(f.part_o, rows * dv * 4, WS, need) && inside(f.part_m, rows * 4, WS, need) &&
+            inside(f.part_l, rows * 4, WS, need) && disjoint(f.part_o, rows * dv * 4, f.part_m, rows * 4) &&
+            disjoint(f.part_m, rows * 4, f.part_l, rows * 4) && disjoint(f.part_o, rows * dv * 4, f.part_l, rows * 4),
+        "partials apart and inside the workspace");
+  if (f.n_splits <= mea::kCombineGroup) return;
+  const size_t r2 = (size_t)((f.n_splits + mea::kCombineGroup - 1) / mea::kCombineGroup) * (size_t)BH * nq;
+  CHECK(inside(f.part2_o, r2 * (dv + 2) * 4, WS, need) && f.part2_m == f.part2_o + r2 * dv && f.part2_l == f.part2_m + r2 &&
+            disjoint(f.part2_o, r2 * (dv + 2) * 4, f.part_o, rows * (dv + 2) * 4),
+        "second partials apart and inside the workspace");
+}
+
+// Unmasked grids just past a whole round of a kernel's workgroups do not run a
+// second, nearly empty one: the plan's rounds, in keys, stay within a third of
+// the work divided evenly over the chip's slots (2000 keys and more in each,
+// where ranges cost little beside them).
+static void check_fwd_rounds(int64_t BH, int64_t nq, int64_t nk, int64_t d, int64_t dv) {
+  check_fwd_grid(BH, nq, nk, d, dv, MEA_BF16, 0);
+  const mea::FwdParams& f = mea::g_last_fwd;
+  const int64_t rows = f.stream_waves ? 128 / f.stream_waves : (d == 64 ? 512 : 256), q_tiles = (nq + rows - 1) / rows;
+  const int64_t slots = 256 * (f.stream_waves == 0 ? 1 : (d == 64 && dv == 64 ? (f.stream_waves == 4 ? 2 : 3) : 2));
+  const int64_t wgs = BH * q_tiles * f.n_splits, rounds = (wgs + slots - 1) / slots;
+  const double even = (double)(BH * q_tiles) * nk / slots;
+  if (even < 2000) return;
+  CHECK((double)(rounds * f.keys_per_split) < 1.34 * even, "%lld x %lld x %lld d %lld: %lld rounds of %lld keys, even %.0f",
+        (long long)BH, (long long)nq, (long long)nk, (long long)d, (long long)rounds, (long long)f.keys_per_split, even);
+}
+
 static void check_bwd_carving(int64_t B, int64_t H, int64_t nq, int64_t d, int dtype, int out_f32, int causal = 0) {
   mea_problem p = prob(B, H, nq, 300, d, dtype, causal, 0, out_f32);
   size_t need = 0;
@@ -196,6 +248,28 @@ int main() {
         for (int64_t nq : {(int64_t)1, (int64_t)100, (int64_t)300, (int64_t)4096, (int64_t)4097})
           check_fwd_plan(1, 1, nq, nk, 64, dt, causal);
   check_fwd_plan(2, 3, 256, 1 << 20, 128, MEA_F16, 0);
+  const struct { int64_t d, dv; } dims[] = {{64, 64}, {128, 128}, {64, 128}, {128, 64}};
+  for (auto w : dims)
+    for (int dt : {MEA_F32, MEA_BF16})
+      for (int causal : {0, 1})
+        for (int64_t bh : {1, 2, 3, 7, 17, 33, 64, 129, 257, 600})
+          for (int64_t nq : {65, 127, 128, 129, 255, 257, 511, 513, 1024, 3071, 3072, 4097, 16384})
+            for (int64_t nk : {1, 31, 33, 64, 127, 129, 255, 511, 513, 1023, 2048, 3071, 3073, 4097, 16383, 16384, 65537, 300001})
+              check_fwd_grid(bh, nq, nk, w.d, w.dv, dt, causal);
+  for (auto w : dims)
+    for (int64_t bh : {1, 3, 9, 17, 33, 65, 100, 129, 200, 255, 257, 300, 400, 513, 600})
+      for (int64_t nq : {512, 1024, 4096, 8192})
+        for (int64_t nk : {16383, 16384, 65536})
+          check_fwd_rounds(bh, nq, nk, w.d, w.dv);
+  // A long causal head alone: ranges, where the heaviest tile would be the call.
+  for (auto w : dims) {
+    check_fwd_grid(1, 16384, 16384, w.d, w.dv, MEA_BF16, 1);
+    CHECK(mea::g_last_fwd.n_splits >= 3, "one long causal head, d %lld: %d ranges", (long long)w.d, mea::g_last_fwd.n_splits);
+  }
+  CHECK(mea::fwd_grid(true, true, 64, 64, 3584, 3584, 16).ranges == 2 &&  // 448 and 476 tiles of 128 queries
+            mea::fwd_grid(true, true, 64, 64, 3584, 3584, 17).ranges == 1 &&
+            mea::fwd_grid(true, true, 64, 64, 3071, 3071, 8).ranges == 1,
+        "causal ranges end with a resident grid, and start at 3072 keys");
   // Both sides of each bound of the causal d = 64 kernel choice.
   for (int64_t nq : {(int64_t)6144, (int64_t)6145})
     check_fwd_plan(2, 64, nq, nq, 64, MEA_BF16, 1);

@@ -21,31 +21,44 @@ GRIDS_16 = [
     (16, 20, 65, 65, 64, 64, True),     # 1 wave, folded order
     (17, 40, 65, 65, 64, 64, True),     # 1 wave, tile-major order (680 workgroups)
     (1, 2, 100, 300, 64, 64, False),    # 4 waves
-    (1, 1, 70, 1100, 64, 64, False),    # 4 waves, 4 ranges
-    (1, 1, 70, 2500, 64, 64, False),    # 2 waves, 4 ranges
-    (13, 10, 65, 2100, 64, 64, False),  # 1 wave, 3 ranges
-    (13, 10, 65, 130, 64, 64, False),   # 2 waves
+    (1, 1, 70, 1100, 64, 64, False),    # 4 waves, 5 ranges
+    (1, 1, 70, 2500, 64, 64, False),    # 4 waves, 10 ranges
+    (13, 10, 65, 2100, 64, 64, False),  # 4 waves
+    (13, 10, 65, 130, 64, 64, False),   # 4 waves
     (20, 30, 65, 33, 64, 64, False),    # 1 wave
     (15, 15, 400, 600, 64, 64, False),  # two-group
-    (2, 2, 500, 9000, 64, 64, False),   # two-group, 17 ranges
+    (2, 2, 500, 9000, 64, 64, False),   # 2 waves, 16 ranges
     (1, 2, 100, 200, 128, 128, False),  # 2 waves
-    (1, 1, 70, 1100, 128, 128, False),  # 2 waves, 4 ranges
+    (1, 1, 70, 1100, 128, 128, False),  # 2 waves, 6 ranges
     (20, 20, 65, 70, 128, 128, False),  # 1 wave
     (1, 2, 100, 100, 128, 128, True),   # 2 waves
     (1, 1, 1100, 1100, 128, 128, True),  # 2 waves, 2 ranges
     (17, 16, 65, 65, 128, 128, True),   # 1 wave
-    (1, 1, 70, 1100, 64, 128, False),   # 2 waves, 2 ranges
-    (5, 8, 65, 2100, 128, 64, False),   # 1 wave, 8 ranges
+    (1, 1, 70, 1100, 64, 128, False),   # 2 waves, 6 ranges
+    (5, 8, 65, 2100, 128, 64, False),   # 1 wave, 11 ranges
     (17, 16, 65, 70, 64, 128, True),    # 1 wave
 ]
 GRIDS_32 = [
-    (1, 1, 70, 300, 64, 64, False),     # 2 waves, 2 ranges
-    (5, 8, 65, 600, 64, 64, False),     # 1 wave, 2 ranges
+    (1, 1, 70, 300, 64, 64, False),     # 1 wave, 2 ranges
+    (5, 8, 65, 600, 64, 64, False),     # 1 wave, 4 ranges
     (5, 8, 129, 129, 64, 64, True),     # 1 wave
     (1, 1, 70, 300, 128, 128, True),    # 2 waves
-    (5, 8, 65, 600, 128, 128, False),   # 1 wave, 2 ranges
+    (5, 8, 65, 600, 128, 128, False),   # 1 wave, 4 ranges
     (1, 1, 70, 300, 64, 128, False),    # 2 waves, 2 ranges
-    (5, 8, 65, 600, 128, 64, False),    # 1 wave, 2 ranges
+    (5, 8, 65, 600, 128, 64, False),    # 1 wave, 4 ranges
+]
+# Grids just past a round, and long causal ones, with the ranges that even them out.
+GRIDS_RANGES = [
+    (3, 11, 1000, 4100, 64, 64, False),   # two-group, 3 ranges
+    (5, 14, 1000, 4100, 64, 64, False),   # two-group, 3 ranges
+    (3, 11, 257, 2100, 128, 128, False),  # two-group, 3 ranges
+    (1, 1, 65, 9000, 128, 128, False),    # 2 waves, 47 ranges: the staged combine
+    (1, 1, 65, 9000, 64, 128, False),     # 2 waves, 47 ranges
+    (10, 15, 100, 2100, 128, 64, False),  # 1 wave, 3 ranges
+    (1, 2, 3100, 3100, 64, 64, True),     # 1 wave, 13 ranges
+    (1, 1, 3100, 3073, 128, 128, True),   # two-group, 13 ranges
+    (1, 1, 3100, 3100, 64, 128, True),    # 1 wave, 13 ranges
+    (1, 1, 3072, 3072, 128, 64, True),    # 1 wave, 13 ranges
 ]
 
 
@@ -70,6 +83,21 @@ def run(shape, dtype, kv_len=None):
 @pytest.mark.parametrize("shape", GRIDS_16, ids=lambda s: "x".join(map(str, s)))
 def test_forward_grids_16bit(shape, dtype):
     run(shape, dtype)
+
+
+@gpu
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("shape", GRIDS_RANGES, ids=lambda s: "x".join(map(str, s)))
+def test_forward_grids_with_ranges(shape, dtype):
+    run(shape, dtype)
+
+
+@gpu
+@pytest.mark.parametrize("shape", [GRIDS_RANGES[0], GRIDS_RANGES[2], GRIDS_RANGES[6], GRIDS_RANGES[7]],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_grids_with_ranges_and_padding(shape):
+    # Valid lengths that leave the later ranges without a key.
+    run(shape, "bf16", kv_len=[200 + 700 * b for b in range(shape[0])])
 
 
 @gpu
