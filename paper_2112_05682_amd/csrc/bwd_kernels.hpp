@@ -2073,7 +2073,8 @@ template <int SW> struct BwdShape<float, 128, SW> {
 };
 
 // dK/dV and dQ in one launch: the first p.n_ktiles * p.bh workgroups (none
-// when dK and dV are not wanted) take key tiles, the rest query tiles.  The
+// when dK and dV are not wanted) take key tiles, the rest query tiles; or the
+// query tiles go first and the key tiles take the rest (p.dq_first).  The
 // two passes read the same inputs and write different outputs, so a grid that
 // does not fill the chip runs them side by side, and a larger one fills the
 // last round of dK/dV with dQ's workgroups.
@@ -2084,7 +2085,9 @@ void attn_bwd_kernel(BwdParams p) {
   using S = BwdShape<T, (D > DV ? D : DV), SW>;
   constexpr int OCC = PARTS == 2 ? S::Q_OCC : S::KV_OCC;
   const int n_kv = (PARTS & 1) && p.dk ? p.n_ktiles * p.bh : 0;
-  const int b = (int)blockIdx.x;
+  // Workgroup b: below n_kv a key tile, from there on a query tile.
+  int b = (int)blockIdx.x;
+  if (sizeof(T) == 2 && !CAUSAL && PARTS == 3 && p.dq_first) b += b < (int)gridDim.x - n_kv ? n_kv : n_kv - (int)gridDim.x;
   // A grid that is resident at once gets one dK/dV and one dQ workgroup per
   // CU, in launch order: with the lightest causal query tiles first a heavy
   // key tile shares its CU with a light query tile (8x8x1024 causal d = 64
@@ -2110,6 +2113,7 @@ static hipError_t launch_bwd_parts(const BwdParams& p, hipStream_t stream) {
   q.n_ktiles = (int)((p.n_k + Dk::BKG - 1) / Dk::BKG);
   constexpr int BQ = 128 * S::QT / SW;
   q.n_qtiles = (int)((p.n_q + BQ - 1) / BQ);
+  q.dq_first = sizeof(T) == 2 && !CAUSAL && PARTS == 3 && bwd_dq_first(D, DV, p.n_q, p.n_k);
   constexpr int kv_lds = Dk::lds_bytes(OCC, __is_same(T, TO));
   constexpr int dq_lds = DqTile<T, D, DV, S::QT, S::BK, SW>::lds_bytes(OCC);
   const int lds = !(PARTS & 1) || !p.dk ? dq_lds : (!(PARTS & 2) || !p.dq || kv_lds > dq_lds ? kv_lds : dq_lds);
@@ -2126,7 +2130,8 @@ template <typename T, typename TO, int D, int DV, int SW, bool CAUSAL>
 static hipError_t launch_bwd_sw(const BwdParams& p, hipStream_t stream) {
   using S = BwdShape<T, (D > DV ? D : DV), SW>;
   if constexpr (S::KV_OCC == S::Q_OCC) {
-    if (SW > 1 || bwd_one_launch(D > DV ? D : DV, p.n_q, p.n_k, p.bh)) return launch_bwd_parts<T, TO, D, DV, SW, 3, CAUSAL>(p, stream);
+    if (SW > 1 || bwd_one_launch(sizeof(T) == 2, CAUSAL, D, DV, p.n_q, p.n_k, p.bh))
+      return launch_bwd_parts<T, TO, D, DV, SW, 3, CAUSAL>(p, stream);
   }
   if constexpr (SW == 1) {
     const hipError_t e = launch_bwd_parts<T, TO, D, DV, SW, 1, CAUSAL>(p, stream);

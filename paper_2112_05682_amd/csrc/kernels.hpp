@@ -115,6 +115,7 @@ struct BwdParams {
   int n_qtiles;  // query tiles of the dQ kernel
   int n_ktiles;  // key tiles of the dK/dV kernel
   int tile_order;  // causal problems: see FwdParams
+  int dq_first;    // one launch: dQ's workgroups before dK/dV's (bwd_dq_first)
   float scale;
   float scale_log2;
   int heads;  // H (bh = b * H + h)
@@ -207,9 +208,26 @@ inline int bwd_stream_waves(bool is16, bool causal, int dmax, int64_t n_q, int64
 // grids at d = 128 the mixed register allocation costs more.  Separate / one
 // launch: d = 64 1x1x4096 162 / 99 us, 8x8x1024 causal 74 / 65, 32x32x1024
 // causal 893 / 859; d = 128 8x16x2048 causal (4096 tiles) 647 / 622, 4x32x4096
-// causal (8192) 2014 / 2042, 4x32x8192 causal 7280 / 7515.
-inline bool bwd_one_launch(int dmax, int64_t n_q, int64_t n_k, int64_t bh) {
-  return dmax == 64 || bwd_tiles128(n_q, n_k, bh) <= 4096;
+// causal (8192) 2014 / 2042, 4x32x8192 causal 7280 / 7515.  Where a few dQ
+// workgroups over many keys are the whole call nothing fills a gap, and that
+// allocation's slower dQ (d = d_v = 128, unmasked) shows: 2x128 on 65536 keys (2 dQ
+// workgroups) 1479 / 1649, 4x512 on 16384 (16) 408 / 428, 2x1782 on 65536 (28) 1641
+// / 1694, but 16x256 on 16384 (32) 463 / 437, 5x128 on 4096 (5) 112 / 112.
+inline bool bwd_one_launch(bool is16, bool causal, int d, int dv, int64_t n_q, int64_t n_k, int64_t bh) {
+  if (is16 && !causal && d == 128 && dv == 128 && n_k > 6144 && bh * ((n_q + 127) / 128) <= 28) return false;
+  return (d == 64 && dv == 64) || bwd_tiles128(n_q, n_k, bh) <= 4096;
+}
+// Order of one launch's two kinds of workgroups, unmasked 16-bit (causal grids and
+// float32 ones start with dK/dV): the longer ones first, so that the short ones fill what they leave.
+// A dQ workgroup streams n_k keys and a dK/dV workgroup n_q queries, about twice
+// as long each (half as much again at d = d_v = 128).  bf16, separate launches / dK/dV
+// first / dQ first, us: d = 64 2x4096 on 62291 keys 1229 / 1454 / 939, 4x4096 on 14081
+// 352 / 385 / 246, 32x1024 on 2185 119 / 95 / 88, but 16x2048 on 4096 153 / 141 / 149,
+// 8x4096 on 4096 180 / 125 / 134; d = 128 32x1024 on 14632 856 / 955 / 782, 16x1498
+// on 2931 168 / 179 / 153, but 5x4096 on 4096 243 / 165 / 189; d = 128, d_v = 64
+// 2x8192 on 12765 752 / 481 / 521.
+inline bool bwd_dq_first(int d, int dv, int64_t n_q, int64_t n_k) {
+  return d == 128 && dv == 128 ? n_k > n_q + n_q / 2 : n_k > 2 * n_q;
 }
 // dtype: 0 float32, 1 fp16, 2 bf16; d and dv the head dimensions of q, k and
 // of v, o.

@@ -270,6 +270,21 @@ int main() {
             mea::fwd_grid(true, true, 64, 64, 3584, 3584, 17).ranges == 1 &&
             mea::fwd_grid(true, true, 64, 64, 3071, 3071, 8).ranges == 1,
         "causal ranges end with a resident grid, and start at 3072 keys");
+  // The longer of dQ's and dK/dV's workgroups start first, and a few long dQ ones
+  // at d = d_v = 128 have a launch of their own.
+  CHECK(mea::bwd_dq_first(64, 64, 100, 201) && !mea::bwd_dq_first(64, 64, 100, 200) &&
+            mea::bwd_dq_first(128, 64, 1, 3) && !mea::bwd_dq_first(64, 128, 4096, 4096) &&
+            mea::bwd_dq_first(128, 128, 100, 151) && !mea::bwd_dq_first(128, 128, 100, 150),
+        "order of one launch");
+  CHECK(!mea::bwd_one_launch(true, false, 128, 128, 3584, 6145, 1) &&
+            mea::bwd_one_launch(true, false, 128, 128, 3585, 6145, 1) &&
+            mea::bwd_one_launch(true, false, 128, 128, 128, 6144, 1) &&
+            mea::bwd_one_launch(true, true, 128, 128, 128, 6145, 1) &&
+            mea::bwd_one_launch(false, false, 128, 128, 128, 6145, 1) &&
+            mea::bwd_one_launch(true, false, 64, 128, 128, 6145, 1) &&
+            mea::bwd_one_launch(true, false, 64, 64, 128, 1 << 20, 64) &&
+            !mea::bwd_one_launch(true, false, 64, 128, 128, 1 << 20, 1),
+        "launches of the 4-wave backward");
   // Both sides of each bound of the causal d = 64 kernel choice.
   for (int64_t nq : {(int64_t)6144, (int64_t)6145})
     check_fwd_plan(2, 64, nq, nq, 64, MEA_BF16, 1);

@@ -25,6 +25,17 @@ GRIDS = [
     (16, 5, 129, 97, 128, 128),     # one, in one launch (240)
     (16, 5, 129, 97, 128, 64),
 ]
+# Unmasked 16-bit, keys for more than twice the queries (1.5 times at d = d_v = 128):
+# dQ's workgroups before dK/dV's in one launch.
+LONG_KEYS = [
+    (1, 2, 33, 67, 64, 64),         # four waves per column
+    (7, 10, 65, 131, 64, 64),       # two
+    (10, 10, 65, 257, 64, 64),      # one
+    (10, 10, 65, 98, 128, 128),
+    (10, 10, 65, 257, 128, 64),
+    (10, 10, 65, 257, 64, 128),
+    (3, 1, 70, 6200, 128, 128),     # one, in two launches (3 dQ workgroups)
+]
 LARGE = [
     ((32, 33, 129, 129, 128, 128), False),  # one, in two launches (4224 tiles)
     ((5, 8, 1030, 1025, 64, 64), False),    # two-group kernels (200 workgroups a pass)
@@ -73,3 +84,9 @@ def test_backward_large_grids(shape, causal):
 def test_backward_shared_columns_with_padding(d, causal):
     # Valid lengths inside, at and past a 32-key share of the staged tile.
     run((5, 1, 70, 129, d, d), "bf16", causal, kv_len=[1, 31, 64, 97, 129])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("shape", LONG_KEYS, ids=lambda s: "x".join(map(str, s)))
+def test_backward_grids_long_keys(shape, dtype):
+    run(shape, dtype, False)
