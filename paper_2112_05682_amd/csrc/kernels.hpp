@@ -162,15 +162,19 @@ constexpr bool bwd_two_group(bool is16, int d, int dv, bool same_out_dtype, bool
 // the same gradients while one wave takes all of a column's rows.  Below one
 // two-group round (256 workgroups) the 4-wave kernels fill more of the chip;
 // causal grids need two rounds before their uneven workgroups even out, and up
-// to 1024 unmasked queries the last 256-query tile is padding to a large part.
+// to 1024 unmasked queries the last 256-query tile is padding to a large part, so
+// that they need long keys and full rounds.
 // Measured, dK/dV + dQ + preprocess in us, 4-wave / two-group, bf16 d = 64:
 // unmasked 1x8x4096 (128 workgroups) 133 / 176, 1x10x4096 (160) 182 / 182,
 // 1x12x4096 (192) 211 / 187, 1x4x8192 (128) 241 / 330, 16x8x600 75 / 96,
-// 8x8x1024 (256) 78 / 77; causal 1x8x8192 (256) 287 / 357, 2x16x4096 (512)
+// 8x8x1024 (256) 78 / 77, 64 heads of 1024 on 16384 keys (256) 1029 / 954, 128 of 900
+// (512) 1966 / 1825, 128 of 1000 on 2048 256 / 261, 64 of 768 on 16384 (192) 749 / 803,
+// 100 of 1024 (400) 1523 / 1568; causal 1x8x8192 (256) 287 / 357, 2x16x4096 (512)
 // 330 / 343, 1x16x8192 (512) 549 / 476, 1x8x16384 (512) 969 / 877.
 inline bool bwd_two_group_fills(bool causal, int64_t n_q, int64_t n_k, int64_t bh) {
   const int64_t wq = bh * ((n_q + 255) / 256), wk = bh * ((n_k + 255) / 256);
-  if (!causal && n_q <= 1024) return false;
+  if (!causal && n_q <= 1024)
+    return n_q > 768 && n_k >= 4096 && wq >= 224 && (wq + 255) / 256 * 256 - wq <= 32;
   return (wq < wk ? wq : wk) >= (causal ? 512 : 160);
 }
 // Workgroups of the 4-wave backward kernels when every wave has 32 rows of its

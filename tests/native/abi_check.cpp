@@ -285,6 +285,11 @@ int main() {
             mea::bwd_one_launch(true, false, 64, 64, 128, 1 << 20, 64) &&
             !mea::bwd_one_launch(true, false, 64, 128, 128, 1 << 20, 1),
         "launches of the 4-wave backward");
+  CHECK(mea::bwd_two_group_fills(false, 769, 4096, 56) && !mea::bwd_two_group_fills(false, 768, 4096, 64) &&
+            !mea::bwd_two_group_fills(false, 1024, 4095, 64) && !mea::bwd_two_group_fills(false, 1024, 4096, 55) &&
+            !mea::bwd_two_group_fills(false, 1024, 4096, 65) && mea::bwd_two_group_fills(false, 1024, 4096, 120) &&
+            mea::bwd_two_group_fills(false, 1025, 4096, 65),
+        "two-group backward of up to 1024 queries");
   // Both sides of each bound of the causal d = 64 kernel choice.
   for (int64_t nq : {(int64_t)6144, (int64_t)6145})
     check_fwd_plan(2, 64, nq, nq, 64, MEA_BF16, 1);

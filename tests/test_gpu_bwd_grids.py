@@ -40,6 +40,8 @@ LARGE = [
     ((32, 33, 129, 129, 128, 128), False),  # one, in two launches (4224 tiles)
     ((5, 8, 1030, 1025, 64, 64), False),    # two-group kernels (200 workgroups a pass)
     ((8, 8, 2049, 2050, 64, 64), True),     # two-group kernels, causal (576)
+    ((8, 8, 1000, 4100, 64, 64), False),    # two-group kernels, a full round of 256 dQ workgroups
+    ((9, 7, 769, 4096, 64, 64), False),     # two-group kernels, 252 of 256
 ]
 
 
