@@ -95,20 +95,10 @@ struct FwdPlan {
   size_t workspace;
 };
 
-void fwd_tiles(int dtype, int64_t d, int64_t dv, bool causal, int64_t n_q, int64_t bh, int* bq, int* bk) {
-  if (dtype == MEA_F32) {
-    *bq = mea::FwdShape<float, 64>::BQ;
-    *bk = mea::FwdShape<float, 64>::BK;
-  } else if (d == 64 && dv == 64) {
-    *bq = mea::FwdShape<__bf16, 64>::BQ == 512 ? mea::fwd64_bq(n_q, bh, causal) : mea::FwdShape<__bf16, 64>::BQ;
-    *bk = mea::FwdShape<__bf16, 64>::BK;
-  } else if (d == 128 && dv == 128) {
-    *bq = mea::FwdShape<__bf16, 128>::BQ == 256 ? mea::fwd128_bq(n_q, causal) : mea::FwdShape<__bf16, 128>::BQ;
-    *bk = mea::FwdShape<__bf16, 128>::BK;
-  } else {  // d_v != d: the 4-wave kernel
-    *bq = mea::kFwdBq4wave128;
-    *bk = mea::FwdShape<__bf16, 128>::BK;
-  }
+// Queries per workgroup of the kernel that the type and head dimensions name.
+int fwd_bq(const mea_problem* p) {
+  if (p->dtype == MEA_F32 || p->d != dv_of(p)) return mea::kFwdBq;
+  return p->d == 64 ? mea::fwd64_bq(p->n_q, p->batch * p->heads, p->causal != 0) : mea::fwd128_bq(p->n_q, p->causal != 0);
 }
 
 // Decode plan: one wave per key range; ranges of at least 4 key tiles, about
@@ -152,12 +142,12 @@ FwdPlan plan_fwd(const mea_problem* p) {
   if (mea::fwd_uses_decode((int)p->dtype, (int)p->d, (int)dv_of(p), p->n_q)) return plan_decode(p);
   FwdPlan pl;
   const int64_t bh = p->batch * p->heads;
-  fwd_tiles(p->dtype, p->d, dv_of(p), p->causal != 0, p->n_q, bh, &pl.bq, &pl.bk);
+  pl.bq = fwd_bq(p);
   pl.n_qtiles = (p->n_q + pl.bq - 1) / pl.bq;
   const mea::FwdGrid g =
       mea::fwd_grid(p->dtype != MEA_F32, p->causal != 0, (int)p->d, (int)dv_of(p), p->n_q, p->n_k, bh);
   pl.stream_waves = g.waves;
-  if (g.waves) pl.bk = mea::fwd_stream_tile(p->dtype != MEA_F32, g.waves);
+  pl.bk = g.waves ? mea::fwd_stream_tile(p->dtype != MEA_F32, g.waves) : 64;
   const int64_t k_tiles = (p->n_k + pl.bk - 1) / pl.bk;
   int64_t splits = g.ranges;
   if (splits > k_tiles) splits = k_tiles;

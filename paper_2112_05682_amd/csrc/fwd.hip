@@ -1277,13 +1277,17 @@ static hipError_t launch_fwd_pp(const FwdParams& p, hipStream_t stream) {
 
 // The 4-wave kernel with SW waves per 32 queries (the plan's choice).
 // Workgroups per CU as their LDS allows: up to 128 staged keys of 64 or 128
-// features, 16-bit or in three parts.
+// features, 16-bit or in three parts.  16-bit d = 64 with one wave: three (166
+// registers, no spills) measured 4-10 % faster than two on causal 4x32x4096, 8x16x2048
+// and 16x16x1024.  float32 d = d_v = 128: two would need 256 registers for 160 of
+// operands' parts and sums and spill (0.90 ms at 2x8x3000 unmasked against 0.60 ms
+// with one; 0.77 ms with float32 MFMAs).
 template <typename T, typename TO, int D, int DV, int SW>
 static hipError_t launch_fwd_sw(const FwdParams& p, bool causal, hipStream_t stream) {
   constexpr bool WIDE = D == 128 || DV == 128, F32 = sizeof(T) == 4;
   if constexpr (SW == 1) {
     constexpr int BK = F32 ? 32 : 64;
-    constexpr int OCC = F32 ? (D == 128 && DV == 128 ? 1 : 2) : (WIDE ? 2 : MEA_T64_FWD_OCC);
+    constexpr int OCC = F32 ? (D == 128 && DV == 128 ? 1 : 2) : (WIDE ? 2 : 3);
     return causal ? launch_fwd_impl<T, TO, D, DV, 1, BK, 1, OCC, true>(p, stream)
                   : launch_fwd_impl<T, TO, D, DV, 1, BK, 1, OCC, false>(p, stream);
   } else {

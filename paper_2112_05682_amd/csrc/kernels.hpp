@@ -239,24 +239,8 @@ inline bool bwd_uses_row_records(int dtype, int d, int dv, bool out_f32, bool ca
   return bwd_two_group(dtype != 0, d, dv, !out_f32, causal, n_q);
 }
 
-// Tile shapes per (element type, head dimension); shared by the host plan
-// and the kernel instantiations.
-// 16-bit d = 64 forward: BQ = 512 selects the two-group ping-pong kernel
-// (8 waves); otherwise the 4-wave kernel runs with QT = BQ / 128 query
-// sub-tiles per wave and MEA_T64_FWD_OCC workgroups per CU.
-#ifndef MEA_T64_FWD_BQ
-#define MEA_T64_FWD_BQ 512
-#endif
-// Three workgroups per CU (166 registers, no spills) measured 4-10 % faster
-// than two on the causal problems this kernel runs (4x32x4096, 8x16x2048,
-// 16x16x1024).
-#ifndef MEA_T64_FWD_OCC
-#define MEA_T64_FWD_OCC 3
-#endif
-template <typename T, int D> struct FwdShape;
-template <> struct FwdShape<__bf16, 64> {
-  static constexpr int BQ = MEA_T64_FWD_BQ, QT = BQ == 512 ? 2 : BQ / 128, BK = 64, OCC = MEA_T64_FWD_OCC;
-};
+// Queries per workgroup of the 4-wave forward with one wave per 32 queries.
+constexpr int kFwdBq = 128;
 // 16-bit d = d_v = 64 causal forward: the two-group kernel (512-query
 // workgroups, returns 512) for problems of more than MEA_T64_FWD_CAUSAL_SMALL
 // queries with at least MEA_T64_FWD_CAUSAL_MIN_PAIRS (batch x heads x n_q^2)
@@ -283,7 +267,7 @@ inline int fwd_causal64_bq(int64_t n_q, int64_t bh) {
   const bool big = n_q > MEA_T64_FWD_CAUSAL_SMALL &&
                    (double)bh * (double)n_q * (double)n_q >= (double)MEA_T64_FWD_CAUSAL_MIN_PAIRS &&
                    bh * ((n_q + 511) / 512) >= MEA_T64_FWD_CAUSAL_MIN_WGS;
-  return big ? 512 : 128;
+  return big ? 512 : kFwdBq;
 }
 // 16-bit d = d_v forward without the causal mask: the 4-wave kernel with
 // 128-query workgroups when the two-group kernel's one query tile (BQ_pp =
@@ -296,34 +280,15 @@ inline int fwd_causal64_bq(int64_t n_q, int64_t bh) {
 // the two-group kernel ahead on the larger problems.
 inline bool fwd_pp_unmasked(int64_t n_q, int bq_pp) { return 2 * n_q > bq_pp; }
 // 16-bit d = d_v = 64 forward: queries per workgroup (512: the two-group
-// kernel; 128: the 4-wave kernel).
+// kernel; 128: the 4-wave kernel).  These two name the kernels' tiles; fwd_grid
+// has the last word and may take the 4-wave kernel where they name the two-group one.
 inline int fwd64_bq(int64_t n_q, int64_t bh, bool causal) {
   if (causal) return fwd_causal64_bq(n_q, bh);
-  return fwd_pp_unmasked(n_q, 512) ? 512 : 128;
+  return fwd_pp_unmasked(n_q, 512) ? 512 : kFwdBq;
 }
-// 16-bit d = 128: BQ = 256 selects the two-group kernel (8 waves of 32
-// queries); 128 the 4-wave kernel.  Problems with d_v != d always run the
-// 4-wave kernel with 128 queries per workgroup (kFwdBq4wave).
-#ifndef MEA_T128_FWD_BQ
-#define MEA_T128_FWD_BQ 256
-#endif
-constexpr int kFwdBq4wave128 = 128;
 // 16-bit d = d_v = 128 forward: 256 (the two-group kernel) or 128 (the 4-wave
-// kernel) queries per workgroup; causal problems always run the two-group
-// kernel.
-inline int fwd128_bq(int64_t n_q, bool causal) {
-  return causal || fwd_pp_unmasked(n_q, MEA_T128_FWD_BQ) ? MEA_T128_FWD_BQ : kFwdBq4wave128;
-}
-template <> struct FwdShape<__bf16, 128> { static constexpr int QT = 1, BK = 64, BQ = MEA_T128_FWD_BQ, OCC = 2; };
-template <> struct FwdShape<_Float16, 64> {
-  static constexpr int BQ = MEA_T64_FWD_BQ, QT = BQ == 512 ? 2 : BQ / 128, BK = 64, OCC = MEA_T64_FWD_OCC;
-};
-template <> struct FwdShape<_Float16, 128> { static constexpr int QT = 1, BK = 64, BQ = MEA_T128_FWD_BQ, OCC = 2; };
-template <> struct FwdShape<float, 64> { static constexpr int QT = 1, BK = 32, BQ = 128, OCC = 2; };
-// float32, d = d_v = 128: two workgroups per CU would need 256 registers for
-// 160 of operands' parts and sums and spill (0.90 ms at 2x8x3000 unmasked
-// against 0.60 ms with one per CU; 0.77 ms with float32 MFMAs).
-template <> struct FwdShape<float, 128> { static constexpr int QT = 1, BK = 32, BQ = 128, OCC = 1; };
+// kernel) queries per workgroup.
+inline int fwd128_bq(int64_t n_q, bool causal) { return causal || fwd_pp_unmasked(n_q, 256) ? 256 : kFwdBq; }
 
 // How a forward that is not decode-shaped fills the chip: the two-group kernel
 // (waves 0; where fwd64_bq or fwd128_bq name it) or the 4-wave kernel with 1, 2
@@ -380,7 +345,8 @@ inline FwdGrid fwd_grid_unmasked(bool is16, int d, int dv, int64_t n_q, int64_t 
   double t_best = 0;
   for (int waves = 0; waves <= (is16 && same && d == 64 ? 4 : 2); waves += waves == 2 ? 2 : 1) {
     // Short streams of the two-group kernel's tiles do not pay for its prologue.
-    if (waves == 0 && !(is16 && same && n_k >= 512 && (d == 64 ? fwd64_bq(n_q, bh, false) : fwd128_bq(n_q, false)) == bq))
+    if (waves == 0 &&
+        !(is16 && same && n_k >= 512 && (d == 64 ? fwd64_bq(n_q, bh, false) : fwd128_bq(n_q, false)) == bq))
       continue;
     const int64_t rows = waves ? 128 / waves : bq, q_wgs = bh * ((n_q + rows - 1) / rows);
     const int64_t bk = waves ? fwd_stream_tile(is16, waves) : 64, k_tiles = (n_k + bk - 1) / bk;
@@ -428,7 +394,7 @@ inline FwdGrid fwd_grid(bool is16, bool causal, int d, int dv, int64_t n_q, int6
   if (!is16) {
     const int w = tiles <= 32 ? 2 : 1;
     const int64_t slots = same && wide ? 256 : 512;
-    return {w, n_k > n_q ? 1 : clamp64(slots / (tiles * w), 1, clamp64(n_k / (w == 2 ? 128 : 256), 1, n_k >= 16384 ? 64 : 8))};
+    return {w, n_k > n_q ? 1 : clamp64(slots / (tiles * w), 1, clamp64(n_k / (w == 2 ? 128 : 256), 1, 8))};
   }
   const bool long_keys = n_q >= 3072 && n_k >= 3072 && n_k <= n_q;
   if (same && d == 64) {
