@@ -481,7 +481,7 @@ __device__ __forceinline__ Frag<T> ld_frag_as(const TO* src, Range<T>& g) {
 // Workgroup id remap for the 8 XCDs of the chip: hardware hands workgroup w to
 // XCD w % 8, so give each XCD a contiguous range of logical tiles (neighbours
 // share K/V in that XCD's L2).  Bijective on [0, n).
-__device__ __forceinline__ int xcd_remap(int w, int n) {
+__host__ __device__ __forceinline__ int xcd_remap(int w, int n) {
   const int x = w & 7, i = w >> 3;
   const int per = n >> 3, rem = n & 7;
   return x * per + (x < rem ? x : rem) + i;
@@ -501,7 +501,7 @@ __device__ __forceinline__ int xcd_remap(int w, int n) {
 struct TileItem {
   int tile, group;
 };
-__device__ __forceinline__ TileItem tile_item(int w, int n, int n_tiles, int order) {
+__host__ __device__ __forceinline__ TileItem tile_item(int w, int n, int n_tiles, int order) {
   if (order == 0) {
     const int g = xcd_remap(w, n);
     return {g % n_tiles, g / n_tiles};

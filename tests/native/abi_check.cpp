@@ -10,7 +10,10 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <vector>
+
 #include "../../include/mea.h"
+#include "../../paper_2112_05682_amd/csrc/device.hpp"
 #include "../../paper_2112_05682_amd/csrc/kernels.hpp"
 
 namespace mea {
@@ -134,6 +137,41 @@ static void check_fwd_grid(int64_t BH, int64_t nq, int64_t nk, int64_t d, int64_
   CHECK(inside(f.part2_o, r2 * (dv + 2) * 4, WS, need) && f.part2_m == f.part2_o + r2 * dv && f.part2_l == f.part2_m + r2 &&
             disjoint(f.part2_o, r2 * (dv + 2) * 4, f.part_o, rows * (dv + 2) * 4),
         "second partials apart and inside the workspace");
+}
+
+// Every order of a causal grid's tiles takes its (tile, group) items once each.
+static void check_tile_order(int n_tiles, int groups) {
+  const int n = n_tiles * groups;
+  for (int order = 0; order < 3; ++order) {
+    std::vector<int> taken(n, 0);
+    for (int w = 0; w < n; ++w) {
+      const mea::TileItem it = mea::tile_item(w, n, n_tiles, order);
+      const bool ok = it.tile >= 0 && it.tile < n_tiles && it.group >= 0 && it.group < groups;
+      CHECK(ok, "order %d of %d x %d: item of workgroup %d", order, n_tiles, groups, w);
+      if (ok) ++taken[it.group * n_tiles + it.tile];
+    }
+    int wrong = 0;
+    for (int t : taken) wrong += t != 1;
+    CHECK(wrong == 0, "order %d of %d x %d: %d items not taken once", order, n_tiles, groups, wrong);
+  }
+}
+
+// The order the launcher gets is causal_tile_order's for the grid it launches:
+// folded orders on the 4-wave kernel's resident grids alone, none unmasked.
+static void check_tile_order_plan(int64_t BH, int64_t nq, int64_t d, int64_t dv, int dtype) {
+  for (int causal = 0; causal < 2; ++causal) {
+    mea_problem p = prob(1, BH, nq, nq, d, dtype, causal, dv == d ? 0 : dv);
+    size_t need = 0;
+    CHECK(mea_attention_fwd_workspace_size(&p, &need) == MEA_OK &&
+              mea_attention_fwd(&p, P, P, P, P, static_cast<float*>(P), nullptr, need ? WS : nullptr, need, nullptr) == MEA_OK,
+          "fwd call");
+    const mea::FwdParams& f = mea::g_last_fwd;
+    const int64_t rows = f.stream_waves ? 128 / f.stream_waves : (d == 64 ? 512 : 256);
+    const int64_t grid = (nq + rows - 1) / rows * BH * f.n_splits, bytes = BH * nq * (d + dv) * (dtype == MEA_F32 ? 4 : 2);
+    const int want = !causal || bytes > (int64_t)128 << 20 ? 0 : (f.stream_waves && grid <= 512 ? 2 : 1);
+    CHECK(f.tile_order == want, "order %d of a %lld-workgroup grid, %lld x %lld, d %lld", f.tile_order, (long long)grid,
+          (long long)BH, (long long)nq, (long long)d);
+  }
 }
 
 // Unmasked grids just past a whole round of a kernel's workgroups do not run a
@@ -261,6 +299,12 @@ int main() {
       for (int64_t nq : {512, 1024, 4096, 8192})
         for (int64_t nk : {16383, 16384, 65536})
           check_fwd_rounds(bh, nq, nk, w.d, w.dv);
+  for (int n_tiles : {1, 2, 3, 5, 8, 9, 16, 31, 64, 511})
+    for (int groups : {1, 2, 7, 8, 32, 57, 64, 101}) check_tile_order(n_tiles, groups);
+  for (auto w : dims)
+    for (int dt : {MEA_F32, MEA_BF16})
+      for (int64_t bh : {1, 32, 64, 65, 257})
+        for (int64_t nq : {65, 1024, 2047, 4096, 8192}) check_tile_order_plan(bh, nq, w.d, w.dv, dt);
   // A long causal head alone: ranges, where the heaviest tile would be the call.
   for (auto w : dims) {
     check_fwd_grid(1, 16384, 16384, w.d, w.dv, MEA_BF16, 1);

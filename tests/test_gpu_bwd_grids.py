@@ -92,3 +92,23 @@ def test_backward_shared_columns_with_padding(d, causal):
 @pytest.mark.parametrize("shape", LONG_KEYS, ids=lambda s: "x".join(map(str, s)))
 def test_backward_grids_long_keys(shape, dtype):
     run(shape, dtype, False)
+
+
+@pytest.mark.parametrize("shape", [
+    (8, 13, 330, 330, 64, 64),    # one launch, resident: dQ's lightest tiles first (624 workgroups)
+    (8, 7, 330, 257, 128, 128),   # one launch, 336
+    (8, 25, 330, 330, 64, 64),    # one launch, several rounds
+], ids=lambda s: "x".join(map(str, s)))
+def test_causal_orders_every_slice(shape):
+    # Grids of more than 256 workgroups and several tiles a head: every slice.
+    B, H, nq, nk, d, dv = shape
+    x = attention_inputs(B, H, nq, nk, d, "bf16", d_v=dv)
+    g = to_gpu(x)
+    o, lse, o_lo = attention_fwd(g["q"], g["k"], g["v"], causal=True, residual=True)
+    got = attention_bwd(g["q"], g["k"], g["v"], o, lse, g["do"], True, o_lo=o_lo)
+    sl = tuple(f64(x[t]) for t in ("q", "k", "v", "do"))
+    ref = oracle.bwd(*sl, scale=d ** -0.5, causal=True)
+    _, rl = oracle.fwd(*sl[:3], scale=d ** -0.5, causal=True)
+    cq, ck = gradient_row_scales(*sl, rl, d ** -0.5, True)
+    for name, a, want, terms in zip(("dQ", "dK", "dV"), got, ref, (cq, ck, None)):
+        check(name, f64(a), want, TOL["bf16"], terms=terms)

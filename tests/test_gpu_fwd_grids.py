@@ -140,6 +140,25 @@ def test_nan_scores_of_one_wave(dtype, d, first):
         assert o.isnan().all() and (lse == -float("inf")).all()
 
 
+@gpu
+@pytest.mark.parametrize("shape", [
+    (8, 13, 330, 330, 64, 64),    # 1 wave, folded (312 workgroups of 3 tiles a head)
+    (7, 8, 330, 257, 128, 128),   # 2 waves, folded (336 of 6)
+    (8, 25, 330, 330, 64, 64),    # 1 wave, tile major (600)
+    (7, 25, 270, 270, 128, 128),  # 1 wave, tile major (525)
+    (8, 8, 600, 600, 64, 128),    # 1 wave, folded (320 of 5)
+], ids=lambda s: "x".join(map(str, s)))
+def test_causal_orders_every_slice(shape):
+    # Grids of more than 256 workgroups and several tiles a head: every slice.
+    B, H, nq, nk, d, dv = shape
+    x = attention_inputs(B, H, nq, nk, d, "bf16", d_v=dv, with_grad=False)
+    g = to_gpu(x)
+    o, lse = attention_fwd(g["q"], g["k"], g["v"], causal=True)
+    ro, rl = oracle.fwd(*(f64(x[t]) for t in ("q", "k", "v")), scale=d ** -0.5, causal=True)
+    check("O", f64(o), ro, TOL["bf16"])
+    check_lse(f64(lse), rl)
+
+
 def test_tile_orders_cover_every_item_once():
     """The three orders of causal_tile_order (tile_item in device.hpp), restated:
     each maps the workgroups of a grid to its (tile, group) items one to one."""
