@@ -165,8 +165,8 @@ struct RowInit {
 };
 
 // A row's initial value, added to products of operands that were split times up.
-template <typename T>
-__device__ __forceinline__ float scaled_init(float x, Range<T>& g) {
+template <typename T, bool UP>
+__device__ __forceinline__ float scaled_init(float x, Range<T, UP>& g) {
   if constexpr (sizeof(T) == 2) {
     return x;
   } else {
@@ -269,8 +269,8 @@ __device__ __forceinline__ Frag<T> lds_col_frag_swz128(const T* tile, int row0, 
 // One workgroup's share of dK and dV: workgroup w of n_wg = p.n_ktiles * p.bh.
 // Returns whether it is to be done again with up = 1 (float32; nothing is
 // written then).
-template <typename T, typename TO, int D, int DV, int QS, int SW, int OCC, bool CAUSAL>
-__device__ __forceinline__ bool dkdv_tile(const BwdParams& p, int w, int n_wg, float up) {
+template <typename T, typename TO, int D, int DV, int QS, int SW, int OCC, bool CAUSAL, bool UP>
+__device__ __forceinline__ bool dkdv_tile(const BwdParams& p, int w, int n_wg) {
   using Cfg = DkdvTile<T, D, DV, QS, SW>;
   using LE = typename Planes<T>::E;  // element of an LDS tile
   constexpr int KWAVES = 4 / SW;  // 32-key columns of the workgroup
@@ -286,7 +286,7 @@ __device__ __forceinline__ bool dkdv_tile(const BwdParams& p, int w, int n_wg, f
   const int h = lane >> 5, c = lane & 31;
 
   const int wave_k = SW > 1 ? wave % KWAVES : wave, wave_q = SW > 1 ? wave / KWAVES : 0;
-  Range<T> range(up);
+  Range<T, UP> range;
   const TileItem item = tile_item(w, n_wg, p.n_ktiles, CAUSAL ? p.tile_order : 0);
   const int kt_idx = item.tile;  // heaviest (earliest keys) first under causal
   const int bh = bh_of_group(item.group, p.bh, p.heads);
@@ -704,7 +704,7 @@ __device__ __forceinline__ bool dkdv_tile(const BwdParams& p, int w, int n_wg, f
     }
   }
 
-  if (wide_range<T>(range, smem_raw)) return true;
+  if (wide_range(range, smem_raw)) return true;
 
   // SW > 1: add the partial sums of the SW waves that share a key column (each
   // took every SW-th 32 QS queries).  The wave with wave_q == i % SW owns
@@ -1241,8 +1241,8 @@ struct DqTile {
 // One workgroup's share of dQ: workgroup w of n_wg = p.n_qtiles * p.bh.  SW waves
 // share 32 QT queries and split the keys between them, BKW keys each of every
 // staged tile.
-template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, int OCC, bool CAUSAL>
-__device__ __forceinline__ bool dq_tile(const BwdParams& p, int w, int n_wg, bool light_first, float up) {
+template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, int OCC, bool CAUSAL, bool UP>
+__device__ __forceinline__ bool dq_tile(const BwdParams& p, int w, int n_wg, bool light_first) {
   constexpr int NT = 256;
   constexpr int QWAVES = 4 / SW;
   constexpr int BQ = QWAVES * 32 * QT;  // queries per workgroup
@@ -1278,7 +1278,7 @@ __device__ __forceinline__ bool dq_tile(const BwdParams& p, int w, int n_wg, boo
   const int h = lane >> 5, c = lane & 31;
 
   const int wave_q = SW > 1 ? wave % QWAVES : wave, wave_k = SW > 1 ? wave / QWAVES : 0;
-  Range<T> range(up);
+  Range<T, UP> range;
   const int ksub = BKW * wave_k;  // first key of this wave in a staged tile
   const TileItem item = tile_item(w, n_wg, p.n_qtiles, CAUSAL ? p.tile_order : 0);
   const int qt_idx = item.tile;
@@ -1553,7 +1553,7 @@ __device__ __forceinline__ bool dq_tile(const BwdParams& p, int w, int n_wg, boo
   for (; it < n_plain; ++it) run(BoolC<false>{}, it);
   for (; it < n_tiles; ++it) run(BoolC<true>{}, it);
 
-  if (wide_range<T>(range, smem_raw)) return true;
+  if (wide_range(range, smem_raw)) return true;
 
   // SW > 1: add the partial sums of the SW waves that share the queries, as in
   // dkdv_tile.
@@ -2094,14 +2094,18 @@ void attn_bwd_kernel(BwdParams p) {
   // 69.6 -> 65.0 us, 1x8x4096 116.8 -> 109.3).  With more rounds the heaviest
   // go first.
   const bool light_first = n_kv > 0 && (int)gridDim.x <= 256 * OCC;
-  float up = range_start<T>(p.scale_log2);
-  if constexpr (PARTS & 1)
-    if (b < n_kv)
-      while (dkdv_tile<T, TO, D, DV, S::QS, SW, OCC, CAUSAL>(p, b, n_kv, up)) up = 1.0f;
-  if constexpr (PARTS & 2)
-    if (b >= n_kv)
-      while (dq_tile<T, TO, D, DV, S::QT, S::BK, SW, OCC, CAUSAL>(p, b - n_kv, (int)gridDim.x - n_kv, light_first, up))
-        up = 1.0f;
+  auto tile = [&](auto up) {
+    if constexpr (PARTS & 1)
+      if (b < n_kv) return dkdv_tile<T, TO, D, DV, S::QS, SW, OCC, CAUSAL, up.value>(p, b, n_kv);
+    if constexpr (PARTS & 2)
+      if (b >= n_kv)
+        return dq_tile<T, TO, D, DV, S::QT, S::BK, SW, OCC, CAUSAL, up.value>(p, b - n_kv, (int)gridDim.x - n_kv,
+                                                                             light_first);
+    return false;
+  };
+  if constexpr (sizeof(T) == 4)
+    if (range_scaled<T>(p.scale_log2) && !tile(BoolC<true>{})) return;
+  tile(BoolC<false>{});
 }
 
 template <typename T, typename TO, int D, int DV, int SW, int PARTS, bool CAUSAL>

@@ -75,34 +75,38 @@ __device__ __forceinline__ f32x16 mma(const Split3& a, const Split3& b, const f3
 // overflow, does its tile again with up = 1 (wide_range), where hi and mid are
 // held to the bf16 range, so that an infinity ends up in lo alone and its
 // products keep their sign.  Beside values above 2^18 those below 2^-110 lose
-// bits.  Scaling and watching cost 2-8 % of the large kernels' time and 1-2 us of
-// the smallest's (2x16x4000 causal, d = 64, forward 412 / 436 us, backward 1347 /
-// 1381; float32 MFMAs 818 and 2406).
-template <typename T> struct Range {
+// bits.  The two are two copies of the code (UP), the second one out of the way:
+// as one, in a loop with `up` in a register, what does not change between the
+// attempts was kept in registers over both, and spilled (d_v != d forwards 50-65
+// registers, now 2-36).  Parts that are never scaled / one copy / two, us: forward,
+// causal 2x8x1000 d = 64 34.8 / 37.3 / 36.4, 2x16x4000 406 / 431 / 423, 2x8x3000 d =
+// 64, d_v = 128 302 / 357 / 309; backward 2x8x1000 82.6 / 88.9 / 84.1, 2x16x4000 1340
+// / 1411 / 1364 (float32 MFMAs 802 and 2403 at the large one).
+template <typename T, bool UP> struct Range {
   static constexpr float up = 1.0f, down = 1.0f, down2 = 1.0f;
-  __device__ __forceinline__ explicit Range(float) {}
   __device__ __forceinline__ void see(float) {}
 };
 constexpr float kRangeUp = 0x1p16f, kRangeTop = 0x1p18f;
-template <> struct Range<float> {
-  float up, down, down2;  // down = 1 / up, down2 = 1 / up^2
-  float top = 0.0f;       // times up
-  __device__ __forceinline__ explicit Range(float u) : up(u), down(1.0f / u), down2(down * down) {}
-  __device__ __forceinline__ void see(float x) { top = fmaxf(top, fabsf(x)); }
+template <bool UP> struct Range<float, UP> {
+  static constexpr float up = UP ? kRangeUp : 1.0f, down = 1.0f / up, down2 = down * down;
+  float top = 0.0f;  // times up
+  __device__ __forceinline__ void see(float x) {
+    if constexpr (UP) top = fmaxf(top, fabsf(x));
+  }
 };
-// `up` to start with (scales so small that scale / up^2 loses bits: 1).
+// Whether to start with the scaled parts (16-bit types have none, and a scale so
+// small that scale / up^2 loses bits does without).
 template <typename T>
-__device__ __forceinline__ float range_start(float scale_log2) {
-  return sizeof(T) == 2 || scale_log2 < 0x1p-90f ? 1.0f : kRangeUp;
+__device__ __forceinline__ bool range_scaled(float scale_log2) {
+  return sizeof(T) == 4 && scale_log2 >= 0x1p-90f;
 }
 // Whether a workgroup of 4 waves must do its tile again (uniform; flags: free
 // LDS, and free again afterwards).
-template <typename T>
-__device__ __forceinline__ bool wide_range(const Range<T>& g, unsigned char* flags) {
-  if constexpr (sizeof(T) == 2) {
+template <typename T, bool UP>
+__device__ __forceinline__ bool wide_range(const Range<T, UP>& g, unsigned char* flags) {
+  if constexpr (sizeof(T) == 2 || !UP) {
     return false;
   } else {
-    if (g.up == 1.0f) return false;
     uint32_t* f = reinterpret_cast<uint32_t*>(flags);
     if ((threadIdx.x & 63) == 0) f[threadIdx.x >> 6] = 0;
     if (g.top > kRangeTop * kRangeUp) f[threadIdx.x >> 6] = 1;
@@ -113,8 +117,11 @@ __device__ __forceinline__ bool wide_range(const Range<T>& g, unsigned char* fla
   }
 }
 
-// The parts of eight computed float32 values.
+// The parts of eight computed float32 values (of the values as rounded: the
+// product that made one must not be contracted with the subtraction of hi, as it
+// would be with up = 1 alone, or the two copies of a tile would differ).
 __device__ __forceinline__ Split3 split8(const float* x, float up) {
+#pragma clang fp contract(off)
   Split3 s;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
@@ -128,16 +135,18 @@ __device__ __forceinline__ Split3 split8(const float* x, float up) {
   }
   return s;
 }
-// The parts of eight float32 values read from memory, of any size.
-__device__ __forceinline__ Split3 split8(const float* x, Range<float>& g) {
+// The parts of eight float32 values read from memory, of any size (scaled: above
+// kRangeTop the result is not used, so nothing holds it to the bf16 range).
+template <bool UP>
+__device__ __forceinline__ Split3 split8(const float* x, Range<float, UP>& g) {
   constexpr float kMax = 0x1.fep127f;  // largest finite bf16
   Split3 s;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const float y = x[e] * g.up;
-    const __bf16 hi = (__bf16)__builtin_amdgcn_fmed3f(y, -kMax, kMax);
+    const __bf16 hi = (__bf16)(UP ? y : __builtin_amdgcn_fmed3f(y, -kMax, kMax));
     const float r1 = y - (float)hi;
-    const __bf16 mid = (__bf16)__builtin_amdgcn_fmed3f(r1, -kMax, kMax);
+    const __bf16 mid = (__bf16)(UP ? r1 : __builtin_amdgcn_fmed3f(r1, -kMax, kMax));
     s.p[0][e] = hi;
     s.p[1][e] = mid;
     s.p[2][e] = (__bf16)(r1 - (float)mid);
@@ -445,8 +454,9 @@ __device__ __forceinline__ Chunk8<T> ld_chunk8(const TO* src) {
     }
   }
 }
-template <typename T>
-__device__ __forceinline__ void st_chunk8(typename Planes<T>::E* dst, int plane, const Chunk8<T>& c, Range<T>& g) {
+template <typename T, bool UP>
+__device__ __forceinline__ void st_chunk8(typename Planes<T>::E* dst, int plane, const Chunk8<T>& c,
+                                          Range<T, UP>& g) {
   if constexpr (sizeof(T) == 2) {
     st16(dst, c);
   } else {
@@ -460,8 +470,8 @@ __device__ __forceinline__ void st_chunk8(typename Planes<T>::E* dst, int plane,
 }
 
 // Eight consecutive elements of a TO array as a fragment of T.
-template <typename T, typename TO>
-__device__ __forceinline__ Frag<T> ld_frag_as(const TO* src, Range<T>& g) {
+template <typename T, typename TO, bool UP>
+__device__ __forceinline__ Frag<T> ld_frag_as(const TO* src, Range<T, UP>& g) {
   if constexpr (sizeof(T) == 2 && __is_same(T, TO)) {
     return *reinterpret_cast<const Frag<T>*>(src);
   } else {

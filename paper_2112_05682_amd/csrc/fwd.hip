@@ -77,8 +77,8 @@ struct FwdTile {
 #endif
 // One workgroup's tile of queries and key range.  Returns whether it is to be
 // done again with up = 1 (float32; nothing is written then).
-template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, int OCC, bool CAUSAL>
-__device__ __forceinline__ bool fwd_tile(const FwdParams& p, float up) {
+template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, int OCC, bool CAUSAL, bool UP>
+__device__ __forceinline__ bool fwd_tile(const FwdParams& p) {
   using Cfg = FwdTile<T, D, DV, QT, BKW, SW, OCC>;
   constexpr int BK = Cfg::BK, QWAVES = 4 / SW;
   using LE = typename Planes<T>::E;  // element of an LDS tile
@@ -95,7 +95,7 @@ __device__ __forceinline__ bool fwd_tile(const FwdParams& p, float up) {
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
   const int h = lane >> 5, c = lane & 31;
-  Range<T> range(up);
+  Range<T, UP> range;
 
   // ---- workgroup -> (split, bh, query tile); heaviest causal tiles first.
   const TileItem item = tile_item(blockIdx.x, gridDim.x, p.n_qtiles, CAUSAL ? p.tile_order : 0);
@@ -391,7 +391,7 @@ __device__ __forceinline__ bool fwd_tile(const FwdParams& p, float up) {
   int it = 0;
   for (; it < n_plain; ++it) step(BoolC<false>{}, it);
   for (; it < n_tiles; ++it) step(BoolC<true>{}, it);
-  if (wide_range<T>(range, smem_raw)) return true;
+  if (wide_range(range, smem_raw)) return true;
 
   // ---- SW > 1: one summary of the waves that share the queries (Section 4's
   // combine): rescale to the common maximum and add, in the order of the
@@ -499,8 +499,9 @@ __device__ __forceinline__ bool fwd_tile(const FwdParams& p, float up) {
 
 template <typename T, typename TO, int D, int DV, int QT, int BKW, int SW, int OCC, bool CAUSAL>
 __global__ __launch_bounds__(256, OCC) void attn_fwd_kernel(FwdParams p) {
-  float up = range_start<T>(p.scale_log2);
-  while (fwd_tile<T, TO, D, DV, QT, BKW, SW, OCC, CAUSAL>(p, up)) up = 1.0f;
+  if constexpr (sizeof(T) == 4)
+    if (range_scaled<T>(p.scale_log2) && !fwd_tile<T, TO, D, DV, QT, BKW, SW, OCC, CAUSAL, true>(p)) return;
+  fwd_tile<T, TO, D, DV, QT, BKW, SW, OCC, CAUSAL, false>(p);
 }
 
 // ---------------------------------------------------------------------------
