@@ -45,6 +45,9 @@
  *   - Supported: d and d_v in {64, 128}; dtype f32, f16 or bf16 (q, k, v and the
  *     gradients share it; o and do share it too unless out_f32 asks for
  *     float32; lse, the workspace and all accumulation are float32).
+ *     f32 operands are multiplied as three bf16 parts each that keep all bits
+ *     of every float32 number; where values above 2^18 are read beside them,
+ *     those below 2^-110 lose their last bits.
  *     Sizes: batch, heads, n_q, n_k >= 1; every element count must fit in
  *     int64 and n_q, n_k <= 2^31 - 1.
  */

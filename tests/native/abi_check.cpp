@@ -73,7 +73,8 @@ static void check_fwd_plan(int64_t B, int64_t H, int64_t nq, int64_t nk, int64_t
   CHECK(st == MEA_OK && mea::g_fwd_calls == before + 1, "fwd call %d", (int)st);
   const mea::FwdParams& f = mea::g_last_fwd;
   if (dtype != MEA_F32 && nq > 64) {
-    // The 16-bit plan tiles the queries as the kernel it picks.
+    // The 16-bit plan's tiles are those of the kernel that the type and sizes name;
+    // a 4-wave grid (stream_waves) makes its own at the launch (check_fwd_grid).
     const int64_t bq = d == 64 ? mea::fwd64_bq(nq, B * H, causal) : mea::fwd128_bq(nq, causal);
     CHECK(f.n_qtiles == (nq + bq - 1) / bq, "query tiles of %lld", (long long)bq);
   }
