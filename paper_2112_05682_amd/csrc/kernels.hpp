@@ -328,15 +328,18 @@ inline FwdRate fwd_rate(bool is16, int d, int dv, int waves) {
 }
 // Unmasked forwards: the kernel and the number of ranges whose rounds take least.
 // n workgroups of L keys on 256 CUs take whole rounds of as many as fit, and a
-// last one of fewer; ranges add a combine (4 us, 6.5 more where it is staged) and
-// the writing and reading of the partial sums.  Only numbers of ranges that fill
-// another CU's worth (n just below a multiple of 256) can be the best.  Counting
+// last one of fewer; ranges add a combine (3 us, 0.3 for each range up to 16 that it
+// reads in a chain, 3 more where it is staged) and the writing and reading of the
+// partial sums.  Only numbers of ranges that fill another CU's worth (n just below a
+// multiple of 256) can be the best, or on a grid that never fills one a few.  Counting
 // rounds finds what thresholds on the same numbers missed, us, thresholds /
 // rounds: d = 64 1x17x8192 459 / 382, 65x1024 on 65536 keys 1988 / 1235, 136x1024
 // on 65536 2567 / 2436; d = 128 40x2000 on 16383 776 / 626, 9x4000 on 262144 5119 /
 // 3988; d = 64, d_v = 128 17x4096 on 16384 760 / 568, d = 128, d_v = 64 17x2048 on
 // 16384 420 / 285; float32 d = 64 24x1500 on 8192 679 / 478, d = 128 17x2048 on
-// 4096 884 / 610.  With at most 3 rounds of ranges in place of 9: 136x1024 on 65536
+// 4096 884 / 610.  The chain of a combine shows on small grids, with it flat at 4 us /
+// as here: d = 64 2x128 on 4096 18.0 / 13.1, 16x65 on 1024 12.3 / 10.4, d = 128 12x129
+// on 3001 23.3 / 19.8.  With at most 3 rounds of ranges in place of 9: 136x1024 on 65536
 // keys d = 64 2940.
 inline FwdGrid fwd_grid_unmasked(bool is16, int d, int dv, int64_t n_q, int64_t n_k, int64_t bh) {
   const bool same = d == dv;
@@ -354,16 +357,21 @@ inline FwdGrid fwd_grid_unmasked(bool is16, int d, int dv, int64_t n_q, int64_t 
     const FwdRate k = fwd_rate(is16, d, dv, waves);
     const int per_cu = k.keys[2] > 0 ? 3 : (k.keys[1] > 0 ? 2 : 1);
     int64_t r_last = 0;
-    for (int64_t m = 0; m <= 9; ++m) {
-      const int64_t r = m == 0 ? 1 : clamp64(256 * m / q_wgs, 1, r_max);
-      if (r == r_last) continue;
+    for (int64_t m = -3; m <= 9; ++m) {
+      const int64_t r = m <= 0 ? (m ? clamp64(2 << -m, 1, r_max) : 1) : clamp64(256 * m / q_wgs, 1, r_max);
+      if (r == r_last || (m < 0 && r * q_wgs > 256)) continue;
       r_last = r;
       const int64_t tiles = (k_tiles + r - 1) / r, ranges = (k_tiles + tiles - 1) / tiles;
       const int64_t on_cu = (q_wgs * ranges + 255) / 256, last = on_cu % per_cu;
-      double t = k.fixed + (double)(tiles * bk) * 1e-3 *
-                               ((double)(on_cu / per_cu) * k.keys[per_cu - 1] + (last ? k.keys[last - 1] : 0));
-      if (ranges > 1) t += 4 + (double)(bh * n_q * ranges * (dv + 2) * 8) * 0.22e-6;
-      if (ranges > kCombineGroup) t += 6.5;
+      double t = (double)(tiles * bk) * 1e-3 *
+                 ((double)(on_cu / per_cu) * k.keys[per_cu - 1] + (last ? k.keys[last - 1] : 0));
+      if (waves == 2 && n_q <= 32) t *= 1.15;  // half the waves have no queries
+      t += k.fixed;
+      if (ranges > 1) {
+        t += 3 + 0.3 * (double)(ranges < kCombineGroup ? ranges : kCombineGroup) +
+             (double)(bh * n_q * ranges * (dv + 2) * 8) * 0.22e-6 + (ranges > kCombineGroup ? 3 : 0);
+        t *= 1.02;  // near ties to one range
+      }
       if (t_best == 0 || t < t_best) {
         t_best = t;
         best = {waves, r};

@@ -22,12 +22,12 @@ GRIDS_16 = [
     (17, 40, 65, 65, 64, 64, True),     # 1 wave, tile-major order (680 workgroups)
     (1, 2, 100, 300, 64, 64, False),    # 4 waves
     (1, 1, 70, 1100, 64, 64, False),    # 4 waves, 5 ranges
-    (1, 1, 70, 2500, 64, 64, False),    # 4 waves, 10 ranges
+    (1, 1, 70, 2500, 64, 64, False),    # 4 waves, 7 ranges
     (13, 10, 65, 2100, 64, 64, False),  # 4 waves
     (13, 10, 65, 130, 64, 64, False),   # 4 waves
     (20, 30, 65, 33, 64, 64, False),    # 1 wave
     (15, 15, 400, 600, 64, 64, False),  # two-group
-    (2, 2, 500, 9000, 64, 64, False),   # 2 waves, 16 ranges
+    (2, 2, 500, 9000, 64, 64, False),   # 4 waves, 8 ranges
     (1, 2, 100, 200, 128, 128, False),  # 2 waves
     (1, 1, 70, 1100, 128, 128, False),  # 2 waves, 6 ranges
     (20, 20, 65, 70, 128, 128, False),  # 1 wave
@@ -35,7 +35,7 @@ GRIDS_16 = [
     (1, 1, 1100, 1100, 128, 128, True),  # 2 waves, 2 ranges
     (17, 16, 65, 65, 128, 128, True),   # 1 wave
     (1, 1, 70, 1100, 64, 128, False),   # 2 waves, 6 ranges
-    (5, 8, 65, 2100, 128, 64, False),   # 1 wave, 11 ranges
+    (5, 8, 65, 2100, 128, 64, False),   # 1 wave, 6 ranges
     (17, 16, 65, 70, 64, 128, True),    # 1 wave
 ]
 GRIDS_32 = [
