@@ -215,10 +215,13 @@ inline int bwd_stream_waves(bool is16, bool causal, int dmax, int64_t n_q, int64
 // causal (8192) 2014 / 2042, 4x32x8192 causal 7280 / 7515.  Where a few dQ
 // workgroups over many keys are the whole call nothing fills a gap, and that
 // allocation's slower dQ (d = d_v = 128, unmasked) shows: 2x128 on 65536 keys (2 dQ
-// workgroups) 1479 / 1649, 4x512 on 16384 (16) 408 / 428, 2x1782 on 65536 (28) 1641
-// / 1694, but 16x256 on 16384 (32) 463 / 437, 5x128 on 4096 (5) 112 / 112.
+// workgroups) 1479 / 1649, 4x512 on 16384 (16) 408 / 428, 1x2048 on 65536 (16) 1551
+// / 1668, but 16x256 on 16384 (32) 463 / 437, 5x128 on 4096 (5) 112 / 112; and not where
+// dK/dV, alone, would take more than a tenth of the time (1x2048 on 16384 449 / 427).
 inline bool bwd_one_launch(bool is16, bool causal, int d, int dv, int64_t n_q, int64_t n_k, int64_t bh) {
-  if (is16 && !causal && d == 128 && dv == 128 && n_k > 6144 && bh * ((n_q + 127) / 128) <= 28) return false;
+  if (is16 && !causal && d == 128 && dv == 128 && n_k > 6144 && bh * ((n_q + 127) / 128) <= 28 &&
+      10 * n_q * ((bh * ((n_k + 127) / 128) + 255) / 256) <= n_k)
+    return false;
   return (d == 64 && dv == 64) || bwd_tiles128(n_q, n_k, bh) <= 4096;
 }
 // Order of one launch's two kinds of workgroups, unmasked 16-bit (causal grids and

@@ -321,8 +321,10 @@ int main() {
             mea::bwd_dq_first(128, 64, 1, 3) && !mea::bwd_dq_first(64, 128, 4096, 4096) &&
             mea::bwd_dq_first(128, 128, 100, 151) && !mea::bwd_dq_first(128, 128, 100, 150),
         "order of one launch");
-  CHECK(!mea::bwd_one_launch(true, false, 128, 128, 3584, 6145, 1) &&
-            mea::bwd_one_launch(true, false, 128, 128, 3585, 6145, 1) &&
+  CHECK(!mea::bwd_one_launch(true, false, 128, 128, 614, 6145, 1) &&
+            mea::bwd_one_launch(true, false, 128, 128, 615, 6145, 1) &&
+            !mea::bwd_one_launch(true, false, 128, 128, 10, 8192, 28) &&
+            mea::bwd_one_launch(true, false, 128, 128, 10, 8192, 29) &&
             mea::bwd_one_launch(true, false, 128, 128, 128, 6144, 1) &&
             mea::bwd_one_launch(true, true, 128, 128, 128, 6145, 1) &&
             mea::bwd_one_launch(false, false, 128, 128, 128, 6145, 1) &&
