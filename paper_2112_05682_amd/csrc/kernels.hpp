@@ -391,8 +391,9 @@ inline FwdGrid fwd_grid_unmasked(bool is16, int d, int dv, int64_t n_q, int64_t 
 // twice the mean of a grid that is resident at once, and ranges of about a round
 // cut it.  us, without / with this rule's choice:
 //   d = 64: 2x8x1024 (tiles 128) two-group 20 / 4 waves 13, 4x8x1024 (256) 20 / 2
-//     waves 16; ranges 1x1x8192 (64) 66 / 33, 1x5x8192 (320) 122 / 92, 1x8x7000
-//     (440) 105 / 102, but 1x10x6000 (470) 92.7 / 95.5
+//     waves 16; ranges 1x1x8192 (64) 66 / 33, 1x5x8192 (320) 122 / 92, 1x12x4096
+//     (384) 63.9 / 61.9, but 1x14x4096 (448) 63.9 / 68.4, 1x8x4096 (256, 2 waves
+//     without) 49.3 / 51.7
 //   d = 128: 1x32x2047 (512) two-group 91 / 1 wave 62, 4x8x1024 (256) 33 / 2
 //     waves 26, 16x16x600 (1280) 68 / 1 wave 63, but 4x32x2047 (2048) 179 / 1
 //     wave 191; ranges 1x1x16384 (128) 266 / 112, 1x5x8192 (320) 206 / 110
@@ -410,7 +411,7 @@ inline FwdGrid fwd_grid(bool is16, bool causal, int d, int dv, int64_t n_q, int6
   const bool long_keys = n_q >= 3072 && n_k >= 3072 && n_k <= n_q;
   if (same && d == 64) {
     if (fwd64_bq(n_q, bh, true) == 512) return {0, 1};
-    if (long_keys && tiles > 32 && tiles <= 448) return {1, (767 + tiles) / tiles};
+    if (long_keys && tiles > 32 && tiles <= 400) return {1, (767 + tiles) / tiles};
     return {tiles <= 128 ? 4 : (tiles <= 256 ? 2 : 1), tiles <= 32 ? clamp64(n_k / 256, 1, 4) : 1};
   }
   if (same) {

@@ -311,8 +311,8 @@ int main() {
     check_fwd_grid(1, 16384, 16384, w.d, w.dv, MEA_BF16, 1);
     CHECK(mea::g_last_fwd.n_splits >= 3, "one long causal head, d %lld: %d ranges", (long long)w.d, mea::g_last_fwd.n_splits);
   }
-  CHECK(mea::fwd_grid(true, true, 64, 64, 3584, 3584, 16).ranges == 2 &&  // 448 and 476 tiles of 128 queries
-            mea::fwd_grid(true, true, 64, 64, 3584, 3584, 17).ranges == 1 &&
+  CHECK(mea::fwd_grid(true, true, 64, 64, 3200, 3200, 16).ranges == 2 &&  // 400 and 425 tiles of 128 queries
+            mea::fwd_grid(true, true, 64, 64, 3200, 3200, 17).ranges == 1 &&
             mea::fwd_grid(true, true, 64, 64, 3071, 3071, 8).ranges == 1,
         "causal ranges end with a resident grid, and start at 3072 keys");
   // The longer of dQ's and dK/dV's workgroups start first, and a few long dQ ones
